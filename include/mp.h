@@ -268,7 +268,10 @@ int mp_diagnostics_static(const mp_state* st, const void* state_buf, int64_t ste
  * (-1 acts as 2).  3D: bx = 256 (64 x 4 tiles) or 512 (64 x 8 tiles, where
  * the tile's LDS ring fits in 64 KiB), seg = z planes per block, vec must be
  * 0 or 1.  0 keeps the current value of a
- * field.  Results do not depend on the tile shape (bitwise). */
+ * field.  Until seg is given here (or by MP_TILE or mp_tune), a launch on a
+ * grid too small to fill the GPU with the default's segments takes shorter
+ * ones; mp_get_tile reports the default.  Results do not depend on the tile
+ * shape (bitwise). */
 int mp_set_tile(mp_state* st, int bx, int seg, int vec);
 int mp_get_tile(const mp_state* st, int* bx, int* seg, int* vec);
 

@@ -82,10 +82,6 @@ __device__ __forceinline__ void at_face3(const R (&pL)[NP], const R (&pR)[NP], c
 
 constexpr int AT3_LANES_OUT = 62;  // written lanes per wave
 constexpr int AT3_WAVES = 4;       // waves per block: consecutive row groups of one strip
-#ifndef MP_AT3_SEG
-#define MP_AT3_SEG 64
-#endif
-constexpr int AT3_SEG = MP_AT3_SEG;  // z planes per wave
 
 // Rows y0-1 .. y0+BY of one z plane at this lane.
 template <typename R, int NP, int NM, int BY>
@@ -125,8 +121,8 @@ __device__ __forceinline__ void at3_dx(const R (&p)[NROW][NP], R h2, R (&t)[NROW
 // GEN: the extended model (x its terms, T - Te = tbase + tslope * row).
 template <typename R, int NP, int NM, int BY, bool GEN>
 __device__ __forceinline__ void antitrap3d_wave(const R* __restrict__ prev, R* __restrict__ next, const Geom& g,
-                                                const AtCoef<R>& c, int nstrips, int nygroups, int nitems,
-                                                const CoefX<R>* x, double tbase, double tslope) {
+                                                const AtCoef<R>& c, int seg, int nstrips, int nygroups,
+                                                int nitems, const CoefX<R>* x, double tbase, double tslope) {
     const int nb = gridDim.x;
     const int q8 = nb / 8;
     const int b = blockIdx.x;
@@ -137,8 +133,8 @@ __device__ __forceinline__ void antitrap3d_wave(const R* __restrict__ prev, R* _
     const int strip = item % nstrips;
     const int rest = item / nstrips;
     const int yg = rest % nygroups;
-    const int z0 = (rest / nygroups) * AT3_SEG;
-    const int z1 = z0 + AT3_SEG < g.nz ? z0 + AT3_SEG : g.nz;
+    const int z0 = (rest / nygroups) * seg;  // seg z planes per wave
+    const int z1 = z0 + seg < g.nz ? z0 + seg : g.nz;
     const int y0 = yg * BY;
     const int craw = strip * AT3_LANES_OUT - 1 + lane;  // -1 .. nx + 62
     const bool ownx = lane >= 1 && lane <= AT3_LANES_OUT && craw < g.nx;
@@ -288,18 +284,18 @@ __device__ __forceinline__ void antitrap3d_wave(const R* __restrict__ prev, R* _
 
 template <typename R, int NP, int NM, int BY>
 __global__ void __launch_bounds__(64 * AT3_WAVES) k_antitrap3d(const R* __restrict__ prev, R* __restrict__ next,
-                                                               Geom g, AtCoef<R> c, int nstrips, int nygroups,
-                                                               int nitems) {
-    antitrap3d_wave<R, NP, NM, BY, false>(prev, next, g, c, nstrips, nygroups, nitems, nullptr, 0.0, 0.0);
+                                                               Geom g, AtCoef<R> c, int seg, int nstrips,
+                                                               int nygroups, int nitems) {
+    antitrap3d_wave<R, NP, NM, BY, false>(prev, next, g, c, seg, nstrips, nygroups, nitems, nullptr, 0.0, 0.0);
 }
 
 // The extended model: the time level and temperature law as the step kernels take them.
 template <typename R, int NP, int NM, int BY>
 __global__ void __launch_bounds__(64 * AT3_WAVES)
-k_antitrap3d_gen(const R* __restrict__ prev, R* __restrict__ next, Geom g, AtCoef<R> c, int nstrips, int nygroups,
-                 int nitems, CoefX<R> x, const int64_t* __restrict__ stepctr, int kstep, double tb0, double tdn,
+k_antitrap3d_gen(const R* __restrict__ prev, R* __restrict__ next, Geom g, AtCoef<R> c, int seg, int nstrips,
+                 int nygroups, int nitems, CoefX<R> x, const int64_t* __restrict__ stepctr, int kstep, double tb0, double tdn,
                  double tslope) {
-    antitrap3d_wave<R, NP, NM, BY, true>(prev, next, g, c, nstrips, nygroups, nitems, &x,
+    antitrap3d_wave<R, NP, NM, BY, true>(prev, next, g, c, seg, nstrips, nygroups, nitems, &x,
                                          tb0 + tdn * (double)(*stepctr + kstep), tslope);
 }
 
@@ -317,10 +313,11 @@ void at_launch3d_kernel(const AtLaunch& L, const AtCoef<R>& c, const CoefX<R>* x
     const R* prev = (const R*)L.prev;
     R* next = (R*)L.next;
     if constexpr (GEN)
-        hipLaunchKernelGGL((k_antitrap3d_gen<R, NP, NM, BY>), grid, block, 0, s, prev, next, L.g, c, nstrips, nyg,
-                           nitems, *x, t->stepctr, t->kstep, t->tb0, t->tdn, t->tslope);
+        hipLaunchKernelGGL((k_antitrap3d_gen<R, NP, NM, BY>), grid, block, 0, s, prev, next, L.g, c, L.seg, nstrips,
+                           nyg, nitems, *x, t->stepctr, t->kstep, t->tb0, t->tdn, t->tslope);
     else
-        hipLaunchKernelGGL((k_antitrap3d<R, NP, NM, BY>), grid, block, 0, s, prev, next, L.g, c, nstrips, nyg, nitems);
+        hipLaunchKernelGGL((k_antitrap3d<R, NP, NM, BY>), grid, block, 0, s, prev, next, L.g, c, L.seg, nstrips, nyg,
+                           nitems);
 }
 
 // GEN: the extended model, x and t its terms and time (unused otherwise).
@@ -328,10 +325,10 @@ template <typename R, bool GEN = false>
 int at_launch3d(const AtLaunch& L, const AtCoef<R>& c, hipStream_t s, const CoefX<R>* x = nullptr,
                 const AtTime* t = nullptr) {
     constexpr int BY = at3_rows<R>();
-    if (L.g.nx < 1 || L.g.ny < 1 || L.g.nz < 1 || (GEN && (!x || !t))) return MP_E_PARAM;
+    if (L.g.nx < 1 || L.g.ny < 1 || L.g.nz < 1 || L.seg < 1 || (GEN && (!x || !t))) return MP_E_PARAM;
     const int nstrips = (L.g.nx + AT3_LANES_OUT - 1) / AT3_LANES_OUT;
     const int nyg = (L.g.ny + BY - 1) / BY;
-    const int64_t items = (int64_t)nstrips * nyg * ((L.g.nz + AT3_SEG - 1) / AT3_SEG);
+    const int64_t items = (int64_t)nstrips * nyg * ((L.g.nz + L.seg - 1) / L.seg);
     if (items > INT32_MAX - AT3_WAVES) return MP_E_PARAM;
     const int nitems = (int)items;
     dim3 block(64 * AT3_WAVES);

@@ -70,6 +70,7 @@ struct mp_state {
     int cur;
     int64_t step;
     int bx, seg, vec;  // vec: cap on cells per lane of the 2D strips (-1: none)
+    bool seg_auto;     // seg is the default's: a launch may shorten it (launch_seg)
     int fuse;  // steps per launch of the step kernel: 1, or 2 (2D single grid)
     int antitrap;  // anti-trapping current: 0 off, 1 on (folded into the 2D step), 2 on (separate correction)
     int graph_chunk;
@@ -496,6 +497,106 @@ int strips_of(const mp_state* st, const Inst& I) {
     return (int)((I.grid.n[0] + w - 1) / w);
 }
 
+// ---- segment length -----------------------------------------------------------
+// A wave (2D strip) or block (3D tile) marches its segment row by row, so a
+// launch lasts about
+//     T(seg) = L + (seg + halo) (alpha + beta k),
+// k the waves each SIMD is dealt: alpha + beta is what a row costs a lone wave
+// (the latency of its instruction chain), beta what it costs a full SIMD.
+// Long segments waste the fewest halo rows, and a grid large enough to fill
+// the chip with them keeps the default; a smaller one is cut into segments
+// short enough for every SIMD to hold a wave.  alpha, beta and the halo are
+// fits to launches timed with 1- to 64-row segments on grids of 64^2 .. 4096^2
+// and 64^3 .. 512^3 (us per row, three phases and two mu fields); other field
+// counts scale by the same work per cell as a batch's items.  Measured, us per
+// step with the default segment and with the one picked: 64^2 FP64 11.3 / 2.3,
+// 512 x 256 FP32 10.0 / 3.9, 1024^2 FP64 20.3 / 14.5, 4096^2 unchanged.  The
+// default stays unless the model expects over 4 % from a shorter one.
+struct SegModel {
+    double halo, alpha, beta;
+};
+constexpr double kSegLaunch = 3.5;  // us of a launch that no row pays for
+constexpr int kChipCus = 256;       // of the part the fits were made on
+
+double cell_weight(int N, int nm) { return 30.0 + 40.0 * N + 26.0 * nm + 14.0 * (N * (N - 1) / 2); }
+
+// Shortest expected launch over the segment lengths 1 .. cap of `rows` rows:
+// `across` work items (waves for 2D, blocks of `wpb` waves for 3D) per segment.
+int best_seg(const SegModel& m, double weight, int64_t across, int64_t rows, int wpb, int cap,
+             double gain = 0.96) {
+    auto cost = [&](int seg) {
+        const int64_t waves = across * ((rows + seg - 1) / seg) * wpb;
+        const double k = (double)((waves + 4 * kChipCus - 1) / (4 * kChipCus));
+        const double len = (double)std::min<int64_t>(seg, rows);
+        return kSegLaunch + weight * (len + m.halo) * (m.alpha + m.beta * k);
+    };
+    int best = cap;
+    double tb = cost(cap) * gain;
+    for (int seg = cap - 1; seg >= 1; --seg) {
+        const double t = cost(seg);
+        if (t < tb) {
+            tb = t;
+            best = seg;
+        }
+    }
+    return best;
+}
+
+// Segment of a single-grid launch of `fuse` steps (at: with the current folded in).
+int launch_seg(const mp_state* st, int fuse, bool at) {
+    if (!st->seg_auto) return st->seg;
+    const Inst& I = st->inst[0];
+    const mp_grid& g = I.grid;
+    const bool f64 = st->precision == MP_FP64;
+    // an anisotropic cell costs about 2.1 times the isotropic one's instructions, a general one 1.4 times
+    const double w = cell_weight(I.N, I.K - 1) / cell_weight(3, 2) * (I.aniso ? 2.1 : 1.0) * (I.ext ? 1.4 : 1.0);
+    if (g.dim == 3) {
+        const SegModel m = f64 ? SegModel{3.0, 0.35, 1.15} : SegModel{3.0, 0.85, 0.21};
+        const int by = st->bx == 512 && !I.ext ? 8 : 4;
+        return best_seg(m, w, ((g.n[0] + 63) / 64) * ((g.n[1] + by - 1) / by), g.n[2], by, st->seg);
+    }
+    SegModel m = f64 ? SegModel{2.0, 0.2, 0.95} : SegModel{2.0, 0.75, 0.37};
+    if (at)
+        m = f64 ? SegModel{3.0, 0.7, 0.95} : SegModel{3.0, 0.7, 0.6};
+    else if (fuse == 1)
+        m.alpha *= 0.5, m.beta *= 0.5;
+    const int64_t out = fuse == 2 || at ? mp::W2X_LANES_OUT_HOST : mp::W2D_LANES_OUT_HOST;
+    const int64_t lane = out * (at || I.ext ? 1 : vec_of(st, I));
+    return best_seg(m, w, (g.n[0] + lane - 1) / lane, g.n[1], 1, st->seg);
+}
+
+// z planes per wave of the 3D correction kernel (strips of 62
+// columns by 2 rows in FP32, 1 in FP64).  Fitted to the same sweeps: 64 planes
+// on 512^3 (973 us); on 200 x 130 x 100 they left half the SIMDs idle (101 us).
+int at3_seg(const mp_state* st) {
+    const Inst& I = st->inst[0];
+    const mp_grid& g = I.grid;
+    const bool f64 = st->precision == MP_FP64;
+    const SegModel m = f64 ? SegModel{3.0, 0.8, 1.2} : SegModel{3.0, 0.75, 0.765};
+    const int rows = f64 ? 1 : 2;
+    return best_seg(m, cell_weight(I.N, I.K - 1) / cell_weight(2, 1), ((g.n[0] + 61) / 62) * ((g.n[1] + rows - 1) / rows),
+                    g.n[2], 1, 64);
+}
+
+// Segment of a batch's work items (one for all its launches: the instance
+// table holds it).
+int batch_seg(const mp_state* st) {
+    if (!st->seg_auto) return st->seg;
+    // as if every strip were as long as the mean one; the uneven deal and the
+    // mirror copies of every strip blur the model, so a shorter segment has to
+    // promise 10 % (8 instances of 64^2 .. 1024^2: 58.0 us per step at 32 rows,
+    // 33.7 at 8; 64 instances: 121.8 at 32, 123.6 at 16)
+    const SegModel m = st->precision == MP_FP64 ? SegModel{3.0, 0.2, 0.95} : SegModel{3.0, 0.75, 0.37};
+    int64_t strips = 0;
+    double rows = 0.0;
+    for (const Inst& I : st->inst) {
+        strips += strips_of(st, I);
+        rows += (double)strips_of(st, I) * (double)I.grid.n[1];
+    }
+    return best_seg(m, 1.0, strips, std::max<int64_t>(1, (int64_t)(rows / (double)strips)), 1, st->seg,
+                    0.9);
+}
+
 // ---- workspace layout -------------------------------------------------------
 // [diag partials + one result record per instance][time level][instance table][work list]
 // [anti-trapping coefficient table][extended-model coefficient table]
@@ -569,9 +670,10 @@ void drop_graphs(mp_state* st) {
 // deals it out.
 void build_items(mp_state* st) {
     st->items.clear();
+    const int seg = batch_seg(st);
     for (size_t i = 0; i < st->inst.size(); ++i) {
         const Inst& I = st->inst[i];
-        const int nseg = (int)((I.grid.n[1] + st->seg - 1) / st->seg);
+        const int nseg = (int)((I.grid.n[1] + seg - 1) / seg);
         const int n = strips_of(st, I) * nseg;
         for (int l = 0; l < n; ++l) st->items.insert(st->items.end(), {(int)i, l});
     }
@@ -581,12 +683,11 @@ void build_items(mp_state* st) {
 
 // Estimated cost of one item: its rows (plus the two-step halo rows) times
 // the strip's width in cells per lane times the work of a cell for (N, K).
-double item_cost(const mp_state* st, const Inst& I, int local) {
+double item_cost(const mp_state* st, const Inst& I, int seg, int local) {
     const int ntx = strips_of(st, I);
-    const int m0 = (local / ntx) * st->seg;
-    const int rows = (int)std::min<int64_t>(st->seg, I.grid.n[1] - m0);
-    const int N = I.N, nm = I.K - 1, pairs = N * (N - 1) / 2;
-    return (rows + 2.0) * vec_of(st, I) * (30.0 + 40.0 * N + 20.0 * nm + 14.0 * pairs + 6.0 * nm);
+    const int m0 = (local / ntx) * seg;
+    const int rows = (int)std::min<int64_t>(seg, I.grid.n[1] - m0);
+    return (rows + 2.0) * vec_of(st, I) * cell_weight(I.N, I.K - 1);
 }
 
 // Deal the work list to the persistent kernel, whose waves of XCD x take the
@@ -598,12 +699,13 @@ double item_cost(const mp_state* st, const Inst& I, int local) {
 // Deterministic; the results do not depend on the order.
 void arrange_items(mp_state* st, int wpx) {
     const int ninst = (int)st->inst.size();
+    const int seg = batch_seg(st);
     std::vector<std::vector<int>> by_inst(ninst);
     std::vector<double> icost(ninst, 0.0);
     for (int it = 0; it < st->nitems; ++it) {
         const int i = st->items[2 * it], l = st->items[2 * it + 1];
         by_inst[i].push_back(l);
-        icost[i] += item_cost(st, st->inst[i], l);
+        icost[i] += item_cost(st, st->inst[i], seg, l);
     }
     std::vector<int> order(ninst);
     for (int i = 0; i < ninst; ++i) order[i] = i;
@@ -624,7 +726,7 @@ void arrange_items(mp_state* st, int wpx) {
         std::vector<std::pair<double, std::pair<int, int>>> v;
         for (int i = 0; i < ninst; ++i)
             if (slice_of[i] == x)
-                for (int l : by_inst[i]) v.push_back({item_cost(st, st->inst[i], l), {i, l}});
+                for (int l : by_inst[i]) v.push_back({item_cost(st, st->inst[i], seg, l), {i, l}});
         std::stable_sort(v.begin(), v.end(), [](const auto& a, const auto& b) { return a.first > b.first; });
         const int w = wpx < 1 ? 1 : wpx;
         for (size_t r0 = 0; r0 < v.size(); r0 += w) {
@@ -640,6 +742,7 @@ void arrange_items(mp_state* st, int wpx) {
 template <typename R>
 int upload_table(mp_state* st) {
     std::vector<mp::InstDesc<R>> tab(st->inst.size());
+    const int seg = batch_seg(st);
     for (size_t i = 0; i < st->inst.size(); ++i) {
         const Inst& I = st->inst[i];
         mp::InstDesc<R>& d = tab[i];
@@ -649,8 +752,8 @@ int upload_table(mp_state* st) {
         d.nm = I.K - 1;
         d.ntx = strips_of(st, I);
         d.vec = vec_of(st, I);
-        d.seg = st->seg;
-        d.nseg = (int)((I.grid.n[1] + st->seg - 1) / st->seg);
+        d.seg = seg;
+        d.nseg = (int)((I.grid.n[1] + seg - 1) / seg);
         d.off = (int64_t)(I.off_bytes / sizeof(R));
         temperature_law(I, d.tb0, d.tdn, d.tslope);
         d.c = make_coef<R>(I);
@@ -790,7 +893,7 @@ int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr
     L.potential = kernel_potential(I.prm.potential);
     L.aniso = I.aniso ? 1 : 0;
     L.bx = st->bx;
-    L.seg = st->seg;
+    L.seg = launch_seg(st, fuse, at_folded(st) && !out1 && !diag);
     L.vec = st->vec;
     L.fuse = fuse;
     L.out1 = out1;
@@ -908,6 +1011,7 @@ void init_state(mp_state* st) {
     for (const Inst& I : st->inst) st->aniso = st->aniso || I.aniso;
     st->precision = st->inst[0].prm.precision;
     st->vec = -1;
+    st->seg_auto = true;
     st->potential = kernel_potential(st->inst[0].prm.potential);
     if (st->inst[0].grid.dim == 3) {
         // measured best on 512^3 FP32: tall tiles, long z segments
@@ -1145,6 +1249,7 @@ int step_antitrapping(mp_state* st, int64_t nsteps, hipStream_t s) {
     A.g = make_geom(I.grid);
     A.nphases = I.N;
     A.nmu = I.K - 1;
+    A.seg = at3_seg(st);
     for (int64_t i = 0; i < nsteps; ++i) {
         mp::KernelCall k;
         int rc = make_step_call(st, (int)i, st->cur, k, 1);
@@ -1459,7 +1564,10 @@ int mp_set_tile(mp_state* st, int bx, int seg, int vec) {
     drop_graphs(st);
     if (bx) st->bx = bx;
     if (vec) st->vec = d3 ? -1 : vec;
-    if (seg) st->seg = seg;
+    if (seg) {
+        st->seg = seg;
+        st->seg_auto = false;
+    }
     if ((seg || vec) && st->batch) {
         const int rc = sync_batch(st);
         if (rc) return rc;
@@ -1511,6 +1619,7 @@ int mp_tune(mp_state* st, const int32_t* cand, int ncand, int reps, double* ms, 
     if (ncand < 1 || reps < 1) return fail(MP_E_PARAM, "ncand and reps must be >= 1");
     hipStream_t s = (hipStream_t)stream;
     const int bx0 = st->bx, seg0 = st->seg, vec0 = st->vec, fuse0 = st->fuse;
+    const bool auto0 = st->seg_auto;
     hipEvent_t e[2] = {nullptr, nullptr};
     int rc = hip_check(hipEventCreate(&e[0]), "hipEventCreate");
     if (rc == MP_OK) rc = hip_check(hipEventCreate(&e[1]), "hipEventCreate");
@@ -1539,6 +1648,8 @@ int mp_tune(mp_state* st, const int32_t* cand, int ncand, int reps, double* ms, 
         const std::string why = rc != MP_OK ? g_err : std::string("no valid tile candidate");
         (void)mp_set_fusion(st, fuse0);
         (void)mp_set_tile(st, bx0, seg0, vec0);
+        st->seg_auto = auto0;
+        if (st->batch) (void)sync_batch(st);
         return fail(rc != MP_OK ? rc : MP_E_PARAM, "mp_tune: %s", why.c_str());
     }
     const int32_t* c = cand + 4 * bi;

@@ -216,6 +216,7 @@ struct AtLaunch {
     void* next;        // state n+1: phi^{n+1} read, mu^{n+1} corrected in place
     Geom g;
     int nphases, nmu;
+    int seg;  // z planes per wave of the 3D correction kernel
 };
 
 template <typename R>
