@@ -209,8 +209,11 @@ int mp_bind(mp_state* st, void* buf0, void* buf1, void* workspace);
  * Each kernel launch reads the current buffer and writes the other one, and
  * performs one step, or two (mp_set_fusion; an odd remainder is a single
  * step), so the current buffer flips once per launch: mp_current
- * reports it.  The time level advances by nsteps.  Results are bitwise the
- * same either way. */
+ * reports it.  On small 2D grids at the default tile a launch performs more
+ * steps (a block steps a region of the grid in LDS); the number of launches
+ * is then even or odd as it would be with two, so the state ends in the same
+ * buffer.  The time level advances by nsteps.  Results are bitwise the same
+ * either way. */
 int mp_step(mp_state* st, int64_t nsteps, void* stream);
 
 /* Which bound buffer (0 or 1) holds the current state, and its time level. */
@@ -270,7 +273,8 @@ int mp_diagnostics_static(const mp_state* st, const void* state_buf, int64_t ste
  * 0 or 1.  0 keeps the current value of a
  * field.  Until seg is given here (or by MP_TILE or mp_tune), a launch on a
  * grid too small to fill the GPU with the default's segments takes shorter
- * ones; mp_get_tile reports the default.  Results do not depend on the tile
+ * ones, and a small 2D grid several steps per launch (mp_step) until any of
+ * the three is given; mp_get_tile reports the default.  Results do not depend on the tile
  * shape (bitwise). */
 int mp_set_tile(mp_state* st, int bx, int seg, int vec);
 int mp_get_tile(const mp_state* st, int* bx, int* seg, int* vec);
@@ -296,8 +300,9 @@ int mp_tune(mp_state* st, const int32_t* cand, int ncand, int reps, double* ms, 
  * With 2, one launch reads a state, computes the next one in registers and
  * writes the one after it, so the state crosses HBM once per two steps
  * (temporal blocking); every cell gets the same arithmetic, and results are
- * bitwise those of two single steps.  Errors: MP_E_PARAM for other values
- * and for 3D states. */
+ * bitwise those of two single steps.  With 1, every launch performs one step;
+ * with 2, a small single grid at the default tile may take more (mp_step).
+ * Errors: MP_E_PARAM for other values and for 3D states. */
 int mp_set_fusion(mp_state* st, int steps);
 int mp_get_fusion(const mp_state* st, int* steps);
 

@@ -71,6 +71,7 @@ struct mp_state {
     int64_t step;
     int bx, seg, vec;  // vec: cap on cells per lane of the 2D strips (-1: none)
     bool seg_auto;     // seg is the default's: a launch may shorten it (launch_seg)
+    bool tile_auto;    // no tile was set: small 2D grids take the tile kernel (tile_plan)
     int fuse;  // steps per launch of the step kernel: 1, or 2 (2D single grid)
     int antitrap;  // anti-trapping current: 0 off, 1 on (folded into the 2D step), 2 on (separate correction)
     int graph_chunk;
@@ -520,20 +521,29 @@ constexpr int kChipCus = 256;       // of the part the fits were made on
 
 double cell_weight(int N, int nm) { return 30.0 + 40.0 * N + 26.0 * nm + 14.0 * (N * (N - 1) / 2); }
 
-// Shortest expected launch over the segment lengths 1 .. cap of `rows` rows:
-// `across` work items (waves for 2D, blocks of `wpb` waves for 3D) per segment.
+// Work of a cell relative to an isotropic one of three phases and two mu
+// fields: anisotropy costs about 2.1 times the instructions, the general
+// kernels 1.4 times.
+double cell_work(const Inst& I) {
+    return cell_weight(I.N, I.K - 1) / cell_weight(3, 2) * (I.aniso ? 2.1 : 1.0) * (I.ext ? 1.4 : 1.0);
+}
+
+// Expected us of a launch over `rows` rows in segments of seg: `across` work
+// items (waves for 2D, blocks of `wpb` waves for 3D) per segment.
+double seg_cost(const SegModel& m, double weight, int64_t across, int64_t rows, int wpb, int seg) {
+    const int64_t waves = across * ((rows + seg - 1) / seg) * wpb;
+    const double k = (double)((waves + 4 * kChipCus - 1) / (4 * kChipCus));
+    const double len = (double)std::min<int64_t>(seg, rows);
+    return kSegLaunch + weight * (len + m.halo) * (m.alpha + m.beta * k);
+}
+
+// Shortest expected launch over the segment lengths 1 .. cap.
 int best_seg(const SegModel& m, double weight, int64_t across, int64_t rows, int wpb, int cap,
              double gain = 0.96) {
-    auto cost = [&](int seg) {
-        const int64_t waves = across * ((rows + seg - 1) / seg) * wpb;
-        const double k = (double)((waves + 4 * kChipCus - 1) / (4 * kChipCus));
-        const double len = (double)std::min<int64_t>(seg, rows);
-        return kSegLaunch + weight * (len + m.halo) * (m.alpha + m.beta * k);
-    };
     int best = cap;
-    double tb = cost(cap) * gain;
+    double tb = seg_cost(m, weight, across, rows, wpb, cap) * gain;
     for (int seg = cap - 1; seg >= 1; --seg) {
-        const double t = cost(seg);
+        const double t = seg_cost(m, weight, across, rows, wpb, seg);
         if (t < tb) {
             tb = t;
             best = seg;
@@ -542,27 +552,35 @@ int best_seg(const SegModel& m, double weight, int64_t across, int64_t rows, int
     return best;
 }
 
+// The 2D strips of `fuse` steps (at: with the current folded in): model and strips per row of segments.
+SegModel strip_model(const mp_state* st, int fuse, bool at) {
+    const bool f64 = st->precision == MP_FP64;
+    if (at) return f64 ? SegModel{3.0, 0.7, 0.95} : SegModel{3.0, 0.7, 0.6};
+    const SegModel m = f64 ? SegModel{2.0, 0.2, 0.95} : SegModel{2.0, 0.75, 0.37};
+    return fuse == 1 ? SegModel{m.halo, 0.5 * m.alpha, 0.5 * m.beta} : m;
+}
+int64_t strip_count(const mp_state* st, int fuse, bool at) {
+    const Inst& I = st->inst[0];
+    const int64_t out = fuse == 2 || at ? mp::W2X_LANES_OUT_HOST : mp::W2D_LANES_OUT_HOST;
+    const int64_t lane = out * (at || I.ext ? 1 : vec_of(st, I));
+    return (I.grid.n[0] + lane - 1) / lane;
+}
+double strip_cost(const mp_state* st, int fuse, int seg) {
+    return seg_cost(strip_model(st, fuse, false), cell_work(st->inst[0]), strip_count(st, fuse, false),
+                    st->inst[0].grid.n[1], 1, seg);
+}
+
 // Segment of a single-grid launch of `fuse` steps (at: with the current folded in).
 int launch_seg(const mp_state* st, int fuse, bool at) {
     if (!st->seg_auto) return st->seg;
     const Inst& I = st->inst[0];
     const mp_grid& g = I.grid;
-    const bool f64 = st->precision == MP_FP64;
-    // an anisotropic cell costs about 2.1 times the isotropic one's instructions, a general one 1.4 times
-    const double w = cell_weight(I.N, I.K - 1) / cell_weight(3, 2) * (I.aniso ? 2.1 : 1.0) * (I.ext ? 1.4 : 1.0);
     if (g.dim == 3) {
-        const SegModel m = f64 ? SegModel{3.0, 0.35, 1.15} : SegModel{3.0, 0.85, 0.21};
+        const SegModel m = st->precision == MP_FP64 ? SegModel{3.0, 0.35, 1.15} : SegModel{3.0, 0.85, 0.21};
         const int by = st->bx == 512 && !I.ext ? 8 : 4;
-        return best_seg(m, w, ((g.n[0] + 63) / 64) * ((g.n[1] + by - 1) / by), g.n[2], by, st->seg);
+        return best_seg(m, cell_work(I), ((g.n[0] + 63) / 64) * ((g.n[1] + by - 1) / by), g.n[2], by, st->seg);
     }
-    SegModel m = f64 ? SegModel{2.0, 0.2, 0.95} : SegModel{2.0, 0.75, 0.37};
-    if (at)
-        m = f64 ? SegModel{3.0, 0.7, 0.95} : SegModel{3.0, 0.7, 0.6};
-    else if (fuse == 1)
-        m.alpha *= 0.5, m.beta *= 0.5;
-    const int64_t out = fuse == 2 || at ? mp::W2X_LANES_OUT_HOST : mp::W2D_LANES_OUT_HOST;
-    const int64_t lane = out * (at || I.ext ? 1 : vec_of(st, I));
-    return best_seg(m, w, (g.n[0] + lane - 1) / lane, g.n[1], 1, st->seg);
+    return best_seg(strip_model(st, fuse, at), cell_work(I), strip_count(st, fuse, at), g.n[1], 1, st->seg);
 }
 
 // z planes per wave of the 3D correction kernel (strips of 62
@@ -790,6 +808,69 @@ bool at_folded(const mp_state* st) { return st->antitrap == 1 && (st->batch || s
 // Steps per launch of the ordinary path.
 int launch_fuse(const mp_state* st) { return st->antitrap ? 1 : st->fuse; }
 
+// The launches of n steps: by the strips or 3D tiles, launch_fuse steps each
+// and single steps for the remainder, or by the 2D tile kernel (tw > 0), evenly.
+// Both make as many launches modulo 2, so the state ends in the same buffer.
+struct Schedule {
+    int64_t n, count;
+    int tw, fuse;
+    int steps(int64_t j) const {
+        if (tw > 0) return (int)(n * (j + 1) / count - n * j / count);
+        return (int)std::min<int64_t>(fuse, n - j * fuse);
+    }
+};
+
+// The tile kernel (tile2d.hpp) pays the launch once per T steps but steps T
+// rim cells around every output cell again, so it serves the grids whose strip
+// launches last little longer than a launch.  A launch of T steps lasts about
+//     kTileBase + r q (a + b T),
+// r the blocks each CU is dealt, a and b per region size, q the cell's work
+// relative to FP32 with three phases and two mu fields; FP64 doubles it where
+// one block's LDS leaves no room for a second block.  Fitted, like SegModel,
+// to launches of 2 .. 12 steps on 64^2 .. 1024^2 (us).  Measured, us per step,
+// strips / tiles: 64^2 N = 2 FP64 2.6 / 1.1; 300 x 70 FP64 3.2 / 2.0, with
+// anisotropy 5.8 / 3.8; 512 x 256 FP32 3.7 / 2.7; 512^2 FP32 4.8 / 4.3; 512^2
+// FP64 5.8 / 6.3, which stays with the strips.
+struct TileModel {
+    int tw;
+    double a, b;
+};
+constexpr TileModel kTileModels[] = {{16, 0.6, 0.16}, {24, 2.1, 0.40}, {32, 2.5, 0.60}};
+constexpr double kTileBase = 5.4;
+constexpr int kTileLeast = 3;  // fewer steps per launch: the strips' two are as good
+
+// parity: the schedule must make as many launches as the strips, modulo 2.
+Schedule schedule(const mp_state* st, int64_t n, bool parity = true) {
+    const int F = launch_fuse(st);
+    Schedule S{n, (n + F - 1) / F, 0, F};
+    if (st->batch || st->antitrap || st->fuse != 2 || !st->tile_auto || st->inst[0].grid.dim != 2) return S;
+    const Inst& I = st->inst[0];
+    const mp_grid& g = I.grid;
+    const int64_t strips = S.count;
+    const int nm = I.K - 1;
+    const double elem = (double)elem_of(st->precision);
+    double best = 0.95 * (double)strips * strip_cost(st, F, launch_seg(st, F, false));
+    for (const TileModel& m : kTileModels)
+        for (int T = kTileLeast; 2 * T < m.tw && T <= n; ++T) {
+            int64_t c = (n + T - 1) / T;
+            if (parity) c += (c ^ strips) & 1;
+            const int most = (int)((n + c - 1) / c);
+            if (n / c < kTileLeast) continue;
+            const int ow = m.tw - 2 * most;
+            const int64_t blocks = ((g.n[0] + ow - 1) / ow) * ((g.n[1] + ow - 1) / ow);
+            const double lds = 2.0 * elem * m.tw * m.tw * (I.N + nm + (I.ext ? nm * nm : nm));
+            const double q = cell_work(I) * (elem == 4.0 ? 1.0 : (lds > 80.0 * 1024.0 ? 1.9 : 1.45));
+            const double r = (double)((blocks + kChipCus - 1) / kChipCus);
+            const double t = (double)c * (kTileBase + r * q * (m.a + m.b * most));
+            if (t < best) {
+                best = t;
+                S.count = c;
+                S.tw = m.tw;
+            }
+        }
+    return S;
+}
+
 // mp_step_diag forms the diagnostics inside the last step launch for single
 // grids without the anti-trapping current, in FP64 2D and in 3D.  The FP32 2D
 // strips take the separate pass: their lane shuffles go through the LDS
@@ -853,12 +934,13 @@ int sync_batch(mp_state* st) {
 }
 
 int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr, int kstep,
-                     mp::KernelCall& k, int fuse = 1, void* out1 = nullptr, const mp::DiagOut* diag = nullptr);
+                     mp::KernelCall& k, int fuse = 1, void* out1 = nullptr, const mp::DiagOut* diag = nullptr,
+                     int tw = 0, int64_t out1stride = 0);
 
 
-// One launch of `fuse` steps (1 or 2; a batch always 1); kstep is the
+// One launch of `fuse` steps (tw > 0: by the tile kernel); kstep is the
 // launch's offset from the device time level.
-int make_step_call(mp_state* st, int kstep, int from, mp::KernelCall& k, int fuse = 1) {
+int make_step_call(mp_state* st, int kstep, int from, mp::KernelCall& k, int fuse = 1, int tw = 0) {
     if (st->batch) {
         mp::BatchLaunch L;
         L.in = st->buf[from];
@@ -875,13 +957,13 @@ int make_step_call(mp_state* st, int kstep, int from, mp::KernelCall& k, int fus
         L.kstep = kstep;
         return batch_call(st, L, k);
     }
-    return make_single_call(st, st->buf[from], st->buf[1 - from], dev_ctr(st), kstep, k, fuse);
+    return make_single_call(st, st->buf[from], st->buf[1 - from], dev_ctr(st), kstep, k, fuse, nullptr, nullptr, tw);
 }
 
 // Single-grid launch of `fuse` steps from ``in`` to ``out`` at time level
 // *ctr + kstep.
 int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr, int kstep,
-                     mp::KernelCall& k, int fuse, void* out1, const mp::DiagOut* diag) {
+                     mp::KernelCall& k, int fuse, void* out1, const mp::DiagOut* diag, int tw, int64_t out1stride) {
     const Inst& I = st->inst[0];
     mp::StepLaunch L;
     L.in = in;
@@ -900,7 +982,19 @@ int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr
     L.stepctr = ctr;
     L.kstep = kstep;
     L.diag = diag;
+    L.tw = tw;
+    L.out1stride = out1stride;
     temperature_law(I, L.tb0, L.tdn, L.tslope);
+    if (tw > 0) {
+        if (st->precision == MP_FP64) {
+            const mp::CoefX<double> x = make_coefx<double>(I);
+            return I.ext ? mp::call_tile<double, true>(L, make_coef<double>(I), &x, k)
+                         : mp::call_tile<double, false>(L, make_coef<double>(I), nullptr, k);
+        }
+        const mp::CoefX<float> x = make_coefx<float>(I);
+        return I.ext ? mp::call_tile<float, true>(L, make_coef<float>(I), &x, k)
+                     : mp::call_tile<float, false>(L, make_coef<float>(I), nullptr, k);
+    }
     if (diag) {
         // the instances that also write the diagnostics' partial records
         // (fused_diag: FP64 2D strips and 3D tiles)
@@ -943,17 +1037,18 @@ int launch(const mp::KernelCall& k, hipStream_t s) {
     return hip_check(hipLaunchKernel(k.func, k.grid, k.block, (void**)k.args, 0, s), "kernel launch");
 }
 
-// Graph of graph_chunk steps starting from buffer `from` (launches of st->fuse
-// steps each), then the time-level advance.  Sets gend[from].
+// Graph of graph_chunk steps starting from buffer `from`, then the time-level
+// advance.  Sets gend[from].
 int build_graph(mp_state* st, int from, hipGraphExec_t* out) {
     std::vector<mp::KernelCall>& calls = st->gcalls[from];
-    const int F = launch_fuse(st);
-    const int nl = st->graph_chunk / F;  // graph_chunk is even, F is 1 or 2
+    const Schedule S = schedule(st, st->graph_chunk);
+    const int nl = (int)S.count;
     calls.assign((size_t)nl + 1, mp::KernelCall());
-    for (int i = 0; i <= nl; ++i) {
+    for (int i = 0, done = 0; i <= nl; ++i) {
         if (i < nl) {
-            const int rc = make_step_call(st, i * F, (from + i) & 1, calls[i], F);
+            const int rc = make_step_call(st, done, (from + i) & 1, calls[i], S.steps(i), S.tw);
             if (rc) return fail(rc, "no kernel instance for this configuration");
+            done += S.steps(i);
         } else {
             mp::call_advance(dev_ctr(st), st->graph_chunk, calls[i]);
         }
@@ -1011,7 +1106,7 @@ void init_state(mp_state* st) {
     for (const Inst& I : st->inst) st->aniso = st->aniso || I.aniso;
     st->precision = st->inst[0].prm.precision;
     st->vec = -1;
-    st->seg_auto = true;
+    st->seg_auto = st->tile_auto = true;
     st->potential = kernel_potential(st->inst[0].prm.potential);
     if (st->inst[0].grid.dim == 3) {
         // measured best on 512^3 FP32: tall tiles, long z segments
@@ -1409,16 +1504,15 @@ int mp_step(mp_state* st, int64_t nsteps, void* stream) {
             st->cur = st->gend[st->cur];
         }
     }
-    // launches of st->fuse steps, then single steps for the remainder
-    for (int64_t i = 0; i < left;) {
-        const int F = left - i >= launch_fuse(st) ? launch_fuse(st) : 1;
+    const Schedule S = schedule(st, left);
+    for (int64_t j = 0, done = 0; j < S.count; ++j) {
         mp::KernelCall k;
-        int rc = make_step_call(st, (int)i, st->cur, k, F);
+        int rc = make_step_call(st, (int)done, st->cur, k, S.steps(j), S.tw);
         if (rc) return fail(rc, "no kernel instance for this configuration");
         rc = launch(k, s);
         if (rc) return rc;
         st->cur = 1 - st->cur;
-        i += F;
+        done += S.steps(j);
     }
     if (left > 0) {
         mp::KernelCall k;
@@ -1562,6 +1656,7 @@ int mp_set_tile(mp_state* st, int bx, int seg, int vec) {
             return fail(MP_E_PARAM, "unsupported cells per lane %d", vec);
     }
     drop_graphs(st);
+    if (bx || seg || vec) st->tile_auto = false;
     if (bx) st->bx = bx;
     if (vec) st->vec = d3 ? -1 : vec;
     if (seg) {
@@ -1619,7 +1714,7 @@ int mp_tune(mp_state* st, const int32_t* cand, int ncand, int reps, double* ms, 
     if (ncand < 1 || reps < 1) return fail(MP_E_PARAM, "ncand and reps must be >= 1");
     hipStream_t s = (hipStream_t)stream;
     const int bx0 = st->bx, seg0 = st->seg, vec0 = st->vec, fuse0 = st->fuse;
-    const bool auto0 = st->seg_auto;
+    const bool seg_auto0 = st->seg_auto, tile_auto0 = st->tile_auto;
     hipEvent_t e[2] = {nullptr, nullptr};
     int rc = hip_check(hipEventCreate(&e[0]), "hipEventCreate");
     if (rc == MP_OK) rc = hip_check(hipEventCreate(&e[1]), "hipEventCreate");
@@ -1648,7 +1743,8 @@ int mp_tune(mp_state* st, const int32_t* cand, int ncand, int reps, double* ms, 
         const std::string why = rc != MP_OK ? g_err : std::string("no valid tile candidate");
         (void)mp_set_fusion(st, fuse0);
         (void)mp_set_tile(st, bx0, seg0, vec0);
-        st->seg_auto = auto0;
+        st->seg_auto = seg_auto0;
+        st->tile_auto = tile_auto0;
         if (st->batch) (void)sync_batch(st);
         return fail(rc != MP_OK ? rc : MP_E_PARAM, "mp_tune: %s", why.c_str());
     }
@@ -1811,18 +1907,26 @@ int mp_adjoint(mp_state* st, const void* ckpt_buf, int64_t nsteps, int64_t every
     auto len_of = [&](int64_t k) { return (nsteps - k * every) < every ? (nsteps - k * every) : every; };
     // Segment k's states, restored from checkpoint k and recomputed into
     // buffer k mod 2, on stream q.
-    // Two steps per launch where the kernel can also store the state between
-    // them (2D single grid at one cell per lane), else one.
+    // Several steps per launch where the kernel can also store the states
+    // between them (the tile kernel; the strips' two at one cell per lane),
+    // else one.
     auto recompute = [&](int64_t k, hipStream_t q) {
         char* seg = w + L.seg[k & 1];
         auto at = [&](int64_t i) { return seg + (size_t)i * L.state; };
         int r = hip_check(hipMemcpyAsync(seg, (const char*)ckpt_buf + (size_t)k * L.state, sb,
                                          hipMemcpyDeviceToDevice, q),
                           "checkpoint restore");
-        for (int64_t i = 0; r == MP_OK && i + 1 < len_of(k);) {
+        const Schedule S = schedule(st, len_of(k) - 1, false);
+        for (int64_t i = 0, j = 0; r == MP_OK && i + 1 < len_of(k);) {
             const int kstep = (int)(n0 + k * every + i);
             mp::KernelCall kc;
-            if (i + 2 < len_of(k) && make_single_call(st, at(i), at(i + 2), zctr, kstep, kc, 2, at(i + 1)) == MP_OK) {
+            if (S.tw > 0) {
+                const int T = S.steps(j++);
+                r = make_single_call(st, at(i), at(i + T), zctr, kstep, kc, T, T > 1 ? at(i + 1) : nullptr, nullptr,
+                                     S.tw, (int64_t)(L.state / elem_of(st->precision)));
+                if (r) return fail(r, "no kernel instance for this configuration");
+                i += T;
+            } else if (i + 2 < len_of(k) && make_single_call(st, at(i), at(i + 2), zctr, kstep, kc, 2, at(i + 1)) == MP_OK) {
                 i += 2;
             } else {
                 r = make_single_call(st, at(i), at(i + 1), zctr, kstep, kc);

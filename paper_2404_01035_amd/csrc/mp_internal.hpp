@@ -90,7 +90,9 @@ struct StepLaunch {
     Geom g;
     int nphases, nmu, dim, potential, aniso;
     int bx, seg, vec;
-    int fuse;  // steps per launch: 1, or 2 (2D single grid)
+    int fuse;  // steps per launch: 1, or 2 (2D single grid), or more (tiles)
+    int tw = 0;  // > 0: the 2D tile kernel on regions of tw x tw cells
+    int64_t out1stride = 0;  // tiles: elements between the states stored at out1 (after steps 1 .. fuse - 1)
     const int64_t* stepctr;
     int kstep;
     double tb0, tdn, tslope;
@@ -167,6 +169,10 @@ int call_step_dim(const StepLaunch& L, const Coef<R>& c, KernelCall& k);
 // tiles in 3D).
 template <typename R, bool D3, bool DIAG = false>
 int call_step_gen(const StepLaunch& L, const Coef<R>& c, const CoefX<R>& x, KernelCall& k);
+// The tile kernel of small 2D grids: L.fuse steps in one launch (x: the
+// extended model's terms, GEN only).
+template <typename R, bool GEN>
+int call_tile(const StepLaunch& L, const Coef<R>& c, const CoefX<R>* x, KernelCall& k);
 template <typename R>
 int call_batch(const BatchLaunch& L, KernelCall& k);
 void call_advance(int64_t* ctr, int64_t by, KernelCall& k);

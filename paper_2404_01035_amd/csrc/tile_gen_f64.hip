@@ -1,0 +1,6 @@
+// General 2D tile kernels (several steps per launch), F64.
+#include "tile2d.hpp"
+
+namespace mp {
+template int call_tile<double, true>(const StepLaunch&, const Coef<double>&, const CoefX<double>*, KernelCall&);
+}
