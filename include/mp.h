@@ -180,7 +180,7 @@ double mp_dt_limit(const mp_grid* grid, int nphases, int ncomp, const mp_params*
  * nphases N in {2, 3}; ncomp K in {2, 3} (K - 1 diffusion potentials).  A
  * problem that uses the extended model (non-zero Bt, Ct, A01, D01 or tau_ab,
  * MP_OBSTACLE_ACTIVE, or the KKS potential MP_THETA) runs the general
- * kernels: one cell per lane in 2D and 64 x 4 tiles in 3D whatever
+ * kernels: one cell per lane in 2D and 32 x 8 tiles in 3D whatever
  * mp_set_tile says (batched instances too, and with the anti-trapping
  * current); the adjoint does not take it.  The KKS variant with MP_WELL runs
  * the plain kernels with its own folded coefficients.
@@ -268,7 +268,7 @@ int mp_diagnostics_static(const mp_state* st, const void* state_buf, int64_t ste
  * vec = the most cells one lane holds (1, 2, or 4 in FP32 only; each lane
  * takes the largest power of two <= vec that divides nx; -1 = the widest the
  * precision allows).  A batched state takes bx = 256 and vec in {-1, 1, 2}
- * (-1 acts as 2).  3D: bx = 256 (64 x 4 tiles) or 512 (64 x 8 tiles, where
+ * (-1 acts as 2).  3D: bx = 256 (32 x 8 tiles) or 512 (64 x 8 tiles, where
  * the tile's LDS ring fits in 64 KiB), seg = z planes per block, vec must be
  * 0 or 1.  0 keeps the current value of a
  * field.  Until seg is given here (or by MP_TILE or mp_tune), a launch on a

@@ -570,15 +570,24 @@ double strip_cost(const mp_state* st, int fuse, int seg) {
                     st->inst[0].grid.n[1], 1, seg);
 }
 
+// Threads per block of a single-grid launch: without a tile set, 3D takes the
+// 256-thread tiles whatever the default (call_3d has both measured).
+int launch_bx(const mp_state* st) { return st->inst[0].grid.dim == 3 && st->tile_auto ? 256 : st->bx; }
+
 // Segment of a single-grid launch of `fuse` steps (at: with the current folded in).
 int launch_seg(const mp_state* st, int fuse, bool at) {
     if (!st->seg_auto) return st->seg;
     const Inst& I = st->inst[0];
     const mp_grid& g = I.grid;
     if (g.dim == 3) {
-        const SegModel m = st->precision == MP_FP64 ? SegModel{3.0, 0.35, 1.15} : SegModel{3.0, 0.85, 0.21};
-        const int by = st->bx == 512 && !I.ext ? 8 : 4;
-        return best_seg(m, cell_work(I), ((g.n[0] + 63) / 64) * ((g.n[1] + by - 1) / by), g.n[2], by, st->seg);
+        // tiles of 32 x 8 (launch_bx 256) or 64 x 8; a 3D face's anisotropy costs
+        // latency, not issue slots (most of it is skipped where |q| is small)
+        const bool f64 = st->precision == MP_FP64;
+        const SegModel m = I.aniso ? (f64 ? SegModel{3.0, 2.0, 1.2} : SegModel{3.0, 1.7, 0.48})
+                                   : (f64 ? SegModel{3.0, 0.55, 0.6} : SegModel{3.0, 0.6, 0.5});
+        const int tx = launch_bx(st) == 512 && !I.ext ? 64 : 32;
+        const double w = cell_weight(I.N, I.K - 1) / cell_weight(3, 2) * (I.ext ? 1.4 : 1.0);
+        return best_seg(m, w, ((g.n[0] + tx - 1) / tx) * ((g.n[1] + 7) / 8), g.n[2], tx / 8, st->seg);
     }
     return best_seg(strip_model(st, fuse, at), cell_work(I), strip_count(st, fuse, at), g.n[1], 1, st->seg);
 }
@@ -960,6 +969,13 @@ int make_step_call(mp_state* st, int kstep, int from, mp::KernelCall& k, int fus
     return make_single_call(st, st->buf[from], st->buf[1 - from], dev_ctr(st), kstep, k, fuse, nullptr, nullptr, tw);
 }
 
+// A state larger than the 256 MiB memory-side cache is gone from it before the
+// next launch reads it, so its stores go past the caches and leave the L2s to
+// the halo rows that neighbouring tiles share: 512^3 FP32 (1.6 GB) 897 -> 873
+// us, 256^3 FP64 of five fields (671 MB) 315 -> 302; a state that the cache
+// holds loses by it, 200^3 FP32 of five fields (160 MB) 105 -> 112 us.
+constexpr double kCachedBytes = 256.0 * 1024 * 1024;
+
 // Single-grid launch of `fuse` steps from ``in`` to ``out`` at time level
 // *ctr + kstep.
 int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr, int kstep,
@@ -969,12 +985,13 @@ int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr
     L.in = in;
     L.out = out;
     L.g = make_geom(I.grid);
+    L.nt = (double)I.bytes > kCachedBytes;
     L.nphases = I.N;
     L.nmu = I.K - 1;
     L.dim = I.grid.dim;
     L.potential = kernel_potential(I.prm.potential);
     L.aniso = I.aniso ? 1 : 0;
-    L.bx = st->bx;
+    L.bx = launch_bx(st);
     L.seg = launch_seg(st, fuse, at_folded(st) && !out1 && !diag);
     L.vec = st->vec;
     L.fuse = fuse;

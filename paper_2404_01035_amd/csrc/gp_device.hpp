@@ -54,6 +54,21 @@ __device__ __forceinline__ double rsqrt_ok(double x) {
     return y * fma(-hx * y, y, 1.5);
 }
 
+// Stores of a new state's cell at element o of every field; NT: past the
+// caches, for a state they cannot hold.
+template <typename R, int NP, int NM, bool NT = false>
+__device__ __forceinline__ void store_cell(R* __restrict__ out, int64_t fs, int64_t o, const R (&phi)[NP],
+                                           const R (&mu)[NM]) {
+#pragma unroll
+    for (int f = 0; f < NP + NM; ++f) {
+        const R v = f < NP ? phi[f < NP ? f : 0] : mu[f < NP ? 0 : f - NP];
+        if constexpr (NT)
+            __builtin_nontemporal_store(v, out + f * fs + o);
+        else
+            out[f * fs + o] = v;
+    }
+}
+
 // Normal component of d(a_c^2 |q|^2)/dq for the four-fold a_c, on the rescaled
 // q.  m = q/|q| comes from one reciprocal square root; the |q|^2 <= guard
 // limit is selected at the end, so lanes do not diverge.

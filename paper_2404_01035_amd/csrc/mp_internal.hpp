@@ -92,6 +92,7 @@ struct StepLaunch {
     int bx, seg, vec;
     int fuse;  // steps per launch: 1, or 2 (2D single grid), or more (tiles)
     int tw = 0;  // > 0: the 2D tile kernel on regions of tw x tw cells
+    bool nt = false;  // 3D: store the new state past the caches
     int64_t out1stride = 0;  // tiles: elements between the states stored at out1 (after steps 1 .. fuse - 1)
     const int64_t* stepctr;
     int kstep;
@@ -165,7 +166,7 @@ int call_step_f32(const StepLaunch& L, const Coef<float>& c, KernelCall& k);
 // state they store (StepLaunch::diag), one per 2D strip wave or 3D tile.
 template <typename R, bool D3, bool DIAG = false>
 int call_step_dim(const StepLaunch& L, const Coef<R>& c, KernelCall& k);
-// The general kernels of the extended model (one cell per lane in 2D, 64 x 4
+// The general kernels of the extended model (one cell per lane in 2D, 32 x 8
 // tiles in 3D).
 template <typename R, bool D3, bool DIAG = false>
 int call_step_gen(const StepLaunch& L, const Coef<R>& c, const CoefX<R>& x, KernelCall& k);

@@ -1,14 +1,23 @@
-// 3D fused phi + mu step: xy tiles staged in an LDS ring of z planes.
+// 3D fused phi + mu step: xy tiles that walk z, neighbours exchanged through LDS.
 //
-// A block owns a 64 (x) by BY (y, 4 or 8) tile and walks a segment of z planes.  A
-// 4-slot LDS ring holds planes m-1, m, m+1 (plus the slot being filled): the
-// loads of plane m+2 are issued into registers before plane m is computed and
-// land in the free slot afterwards, so one barrier per plane suffices.  Each
-// staged cell also stores its scaled mobility M~ so that faces never recompute
-// h of a neighbour.  The z face between planes m and m+1 stays in registers
-// (its W, J) and becomes the lower face of plane m+1; in-plane faces are
-// evaluated by both of their cells with identical code and inputs.  Blocks are
-// dealt XCD-aware so that a band of tiles shares one XCD's L2.
+// A block owns a BX (x) by BY (y) tile, one thread per column, and walks a
+// segment of z planes.  Each staged cell also stores its scaled mobility M~ so
+// that faces never recompute h of a neighbour.  The z face between planes m and
+// m+1 stays in registers (its W, J) and becomes the lower face of plane m+1;
+// in-plane faces are evaluated by both of their cells with identical code and
+// inputs.  Blocks are dealt XCD-aware so that a band of tiles shares one XCD's
+// L2.  What the planes keep in LDS sets how many blocks a CU holds, and both
+// forms below need all they can get: the kernel is bound by the latency of the
+// march (a barrier per plane), not by one unit.
+//
+// Isotropic faces see only the two cells they separate, so a plane's neighbours
+// are read in that plane alone: two slots alternate (the plane being computed,
+// the next one being filled), and the cell above, the z face's other side, is
+// the thread's own and stays in registers.
+//
+// Anisotropic faces also see the tangential differences of phi on the planes
+// above and below: phi keeps a ring of four planes (m-1, m, m+1 and the one
+// being filled), mu and M~ a ring of three (m, m+1 and the one being filled).
 #pragma once
 
 #include "diag_cell.hpp"
@@ -16,148 +25,328 @@
 
 namespace mp {
 
-// The step of one block (GEN: the extended model's arithmetic, x its terms).
-template <typename R, int NP, int NM, bool ANISO, bool OBST, int BX, int BY, bool GEN, bool DIAG = false>
-__device__ __forceinline__ void step3d_block(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
-                                             const Coef<R>& c, const int64_t* __restrict__ stepctr, int kstep,
-                                             double tb0, double tdn, double tslope, int seg, int ntx, int nty,
-                                             const CoefX<R>* x, DiagAcc* da = nullptr,
-                                             const DiagCoef* dc = nullptr) {
+// Tile of a block and what its threads stage: position 0 is the thread's own
+// cell, the others lie on the halo ring (CORNERS: with its corners, which only
+// tangential differences read).
+template <int BX, int BY, bool CORNERS>
+struct Tile3d {
+    static constexpr int PW = BX + 2;
+    static constexpr int PP = PW * (BY + 2);
+    static constexpr int NT = BX * BY;
+    static constexpr int ROW = CORNERS ? PW : BX;  // cells of the rows above and below
+    static constexpr int NHALO = 2 * ROW + 2 * BY;
+    static constexpr int NPOS = 1 + (NHALO + NT - 1) / NT;
+
+    int x0, y0, m0, m1;
+    int64_t off[NPOS];  // in-plane element offset of each staged cell
+    int pos[NPOS];      // its LDS position
+    int tid;
+
+    __device__ __forceinline__ bool has(int k) const { return k == 0 || tid + (k - 1) * NT < NHALO; }
+
+    __device__ __forceinline__ void init(const Geom& g, int seg, int ntx, int nty) {
+        const int nb = gridDim.x;
+        const int q8 = nb / 8;
+        const int b = blockIdx.x;
+        const int tile = (b < 8 * q8) ? (b % 8) * q8 + b / 8 : b;
+        const int rest = tile / ntx;
+        x0 = (tile % ntx) * BX;
+        y0 = (rest % nty) * BY;
+        m0 = (rest / nty) * seg;
+        m1 = min(m0 + seg, g.nz);
+        tid = threadIdx.x;
+        const bool perx = g.bcx == MP_BC_PERIODIC;
+        const bool pery = g.bcy == MP_BC_PERIODIC;
+#pragma unroll
+        for (int k = 0; k < NPOS; ++k) {
+            int ix = 1 + tid % BX, iy = 1 + tid / BX;
+            if (k > 0) {
+                const int q = tid + (k - 1) * NT;
+                if (q < 2 * ROW) {
+                    iy = q < ROW ? 0 : BY + 1;
+                    ix = (q < ROW ? q : q - ROW) + (CORNERS ? 0 : 1);
+                } else {
+                    const int w = min(q - 2 * ROW, 2 * BY - 1);
+                    iy = 1 + (w >> 1);
+                    ix = (w & 1) * (PW - 1);
+                }
+            }
+            pos[k] = iy * PW + ix;
+            off[k] = gmap(x0 - 1 + ix, g.nx, perx) + gmap(y0 - 1 + iy, g.ny, pery) * (int64_t)g.nx;
+        }
+    }
+};
+
+// New values of a column's cell written at out + o (and added to the diagnostics).
+template <typename R, int NP, int NM, bool GEN, bool DIAG, bool NT>
+__device__ __forceinline__ void store3d(R* __restrict__ out, const Geom& g, int64_t o, const R (&phin)[NP],
+                                        const R (&mun)[NM], int gy, DiagAcc* da, const DiagCoef* dc) {
+    store_cell<R, NP, NM, NT>(out, g.fstride, o, phin, mun);
+    if constexpr (DIAG) {
+        double p[NP], u[NM];
+#pragma unroll
+        for (int a = 0; a < NP; ++a) p[a] = (double)phin[a];
+#pragma unroll
+        for (int k = 0; k < NM; ++k) u[k] = (double)mun[k];
+        diag_cell<NP, NM, GEN>(p, u, dc->tt0 + dc->tslope * (double)gy, *dc, *da);
+    }
+}
+
+// The isotropic step of one block (GEN: the extended model's arithmetic, x its terms).
+template <typename R, int NP, int NM, bool OBST, int BX, int BY, bool GEN, bool DIAG, bool NT>
+__device__ __forceinline__ void step3d_iso(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
+                                           const Coef<R>& c, const int64_t* __restrict__ stepctr, int kstep,
+                                           double tb0, double tdn, double tslope, int seg, int ntx, int nty,
+                                           const CoefX<R>* x, DiagAcc* da, const DiagCoef* dc) {
     constexpr int NF = NP + NM;
     constexpr int NMM = mob_n<NM, GEN>();
-    constexpr int PW = BX + 2;
-    constexpr int PH = BY + 2;
-    constexpr int PP = PW * PH;
-    constexpr int NT = BX * BY;
-    constexpr int NPOS = (PP + NT - 1) / NT;
-    constexpr int NS = 4;
-    __shared__ R sv[NS][NF][PP];
-    __shared__ R sm[NS][NMM][PP];
-
-    const int nb = gridDim.x;
-    const int q8 = nb / 8;
-    const int b = blockIdx.x;
-    const int tile = (b < 8 * q8) ? (b % 8) * q8 + b / 8 : b;
-    const int tx_i = tile % ntx;
-    const int rest = tile / ntx;
-    const int ty_i = rest % nty;
-    const int sg_i = rest / nty;
-
-    const int x0 = tx_i * BX;
-    const int y0 = ty_i * BY;
-    const int m0 = sg_i * seg;
-    const int m1 = min(m0 + seg, g.nz);
-    const bool perx = g.bcx == MP_BC_PERIODIC;
-    const bool pery = g.bcy == MP_BC_PERIODIC;
+    typedef Tile3d<BX, BY, false> Tile;
+    constexpr int PW = Tile::PW, PP = Tile::PP, NPOS = Tile::NPOS;
+    __shared__ R sv[2][NF][PP];
+    __shared__ R sm[2][NMM][PP];
+    Tile t;
+    t.init(g, seg, ntx, nty);
     const bool perz = g.bcz == MP_BC_PERIODIC;
-    const int64_t sy = g.nx;
     const int64_t sz = (int64_t)g.nx * g.ny;
     const int64_t fs = g.fstride;
 
-    const int tid = threadIdx.x;
-    const int lx = tid % BX;
-    const int ly = tid / BX;
-
-    // Tile positions as loaded: the first (BY + 2) * BX are the halo rows'
-    // interior columns, one aligned BX-wide row segment per wave; the last
-    // 2 (BY + 2) are the rows' two halo columns.  ppos[k] is the LDS position
-    // (row * PW + column) of this thread's k-th load.
-    constexpr int NCORE = (BY + 2) * BX;
-    int64_t poff[NPOS];
-    int ppos[NPOS];
+    // the thread's own cell of one plane
+    struct Cell {
+        R phi[NP], mu[NM], h[NP], Mt[NMM];
+    };
+    R reg[NPOS][NF];
+    auto fetch = [&](int m) {
+        const R* p = in + (int64_t)gmap(m, g.nz, perz) * sz;
 #pragma unroll
-    for (int k = 0; k < NPOS; ++k) {
-        int q = tid + k * NT;
-        if (q >= PP) q = PP - 1;
-        int ix, iy;
-        if (q < NCORE) {
-            iy = q / BX;
-            ix = 1 + q % BX;
-        } else {
-            iy = (q - NCORE) >> 1;
-            ix = ((q - NCORE) & 1) * (PW - 1);
-        }
-        ppos[k] = iy * PW + ix;
-        poff[k] = gmap(x0 - 1 + ix, g.nx, perx) + gmap(y0 - 1 + iy, g.ny, pery) * sy;
+        for (int k = 0; k < NPOS; ++k)
+            if (t.has(k)) {
+#pragma unroll
+                for (int f = 0; f < NF; ++f) reg[k][f] = p[f * fs + t.off[k]];
+            }
+    };
+    auto own = [&](Cell& C) {
+#pragma unroll
+        for (int a = 0; a < NP; ++a) C.phi[a] = reg[0][a];
+#pragma unroll
+        for (int k = 0; k < NM; ++k) C.mu[k] = reg[0][NP + k];
+        interp_h<R, NP>(C.phi, C.h);
+        mobility_any<R, NP, NM, GEN>(C.h, c, x, C.Mt);
+    };
+    auto stage = [&](int m, const Cell& C) {
+        const int sl = m & 1;
+#pragma unroll
+        for (int k = 0; k < NPOS; ++k)
+            if (t.has(k)) {
+                R Mt[NMM];
+                if (k == 0) {
+#pragma unroll
+                    for (int kk = 0; kk < NMM; ++kk) Mt[kk] = C.Mt[kk];
+                } else {
+                    R ph[NP], hh[NP];
+#pragma unroll
+                    for (int a = 0; a < NP; ++a) ph[a] = reg[k][a];
+                    interp_h<R, NP>(ph, hh);
+                    mobility_any<R, NP, NM, GEN>(hh, c, x, Mt);
+                }
+#pragma unroll
+                for (int f = 0; f < NF; ++f) sv[sl][f][t.pos[k]] = reg[k][f];
+#pragma unroll
+                for (int kk = 0; kk < NMM; ++kk) sm[sl][kk][t.pos[k]] = Mt[kk];
+            }
+    };
+    const R tau[1][NP] = {};
+    // face between the cell C and its in-plane neighbour at LDS position p
+    auto face = [&](int sl, const Cell& C, int p, bool below, R(&U)[NP], R(&W)[NP], R(&J)[NM]) {
+        R pn[NP], un[NM], mn[NMM];
+#pragma unroll
+        for (int a = 0; a < NP; ++a) pn[a] = sv[sl][a][p];
+#pragma unroll
+        for (int k = 0; k < NM; ++k) un[k] = sv[sl][NP + k][p];
+#pragma unroll
+        for (int k = 0; k < NMM; ++k) mn[k] = sm[sl][k][p];
+        if (below)
+            face_core<R, NP, NM, false, 0, GEN>(pn, C.phi, tau, mn, C.Mt, un, C.mu, c, U, W, J);
+        else
+            face_core<R, NP, NM, false, 0, GEN>(C.phi, pn, tau, C.Mt, mn, C.mu, un, c, U, W, J);
+    };
+
+    const int gx = t.x0 + t.tid % BX;
+    const int gy = t.y0 + t.tid / BX;
+    const bool valid = gx < g.nx && gy < g.ny;
+    const int64_t o0 = (int64_t)gx + (int64_t)gy * g.nx;
+    const int pc = t.pos[0];
+    const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
+    R Cs[NP];  // T - Te depends on y only
+    const R tt = (R)(tbase + tslope * (double)gy);
+    psi_const_any<R, NP, GEN>(tt, c, x, Cs);
+
+    Cell A, B;
+    R Wlo[NP], Jlo[NM];  // z face between planes m-1 and m
+    fetch(t.m0 - 1);
+    own(B);
+    fetch(t.m0);
+    own(A);
+    stage(t.m0, A);
+    fetch(t.m0 + 1);
+    {
+        R Ud[NP];
+        face_core<R, NP, NM, false, 0, GEN>(B.phi, A.phi, tau, B.Mt, A.Mt, B.mu, A.mu, c, Ud, Wlo, Jlo);
     }
+    __syncthreads();
+
+    // plane m with its own cells in C; leaves plane m+1's in N
+    auto plane = [&](int m, const Cell& C, Cell& N) {
+        own(N);
+        if (m + 1 < t.m1) stage(m + 1, N);
+        if (m + 2 <= t.m1) fetch(m + 2);
+        const int sl = m & 1;
+        R Gs[NP], Js[NM];
+        {
+            R Ul[NP], Wl[NP], Jl[NM], Uh[NP], Wh[NP], Jh[NM];
+            face(sl, C, pc - 1, true, Ul, Wl, Jl);
+            face(sl, C, pc + 1, false, Uh, Wh, Jh);
+#pragma unroll
+            for (int a = 0; a < NP; ++a) Gs[a] = Uh[a] - Wl[a];
+#pragma unroll
+            for (int k = 0; k < NM; ++k) Js[k] = Jh[k] - Jl[k];
+        }
+        {
+            R Ul[NP], Wl[NP], Jl[NM], Uh[NP], Wh[NP], Jh[NM];
+            face(sl, C, pc - PW, true, Ul, Wl, Jl);
+            face(sl, C, pc + PW, false, Uh, Wh, Jh);
+#pragma unroll
+            for (int a = 0; a < NP; ++a) Gs[a] = Gs[a] + (Uh[a] - Wl[a]);
+#pragma unroll
+            for (int k = 0; k < NM; ++k) Js[k] = Js[k] + (Jh[k] - Jl[k]);
+        }
+        {
+            R Uh[NP], Wh[NP], Jh[NM];
+            face_core<R, NP, NM, false, 0, GEN>(C.phi, N.phi, tau, C.Mt, N.Mt, C.mu, N.mu, c, Uh, Wh, Jh);
+#pragma unroll
+            for (int a = 0; a < NP; ++a) {
+                Gs[a] = Gs[a] + (Uh[a] - Wlo[a]);
+                Wlo[a] = Wh[a];
+            }
+#pragma unroll
+            for (int k = 0; k < NM; ++k) {
+                Js[k] = Js[k] + (Jh[k] - Jlo[k]);
+                Jlo[k] = Jh[k];
+            }
+        }
+        R phin[NP], mun[NM], h1[NP];
+        cell_update_any<R, NP, NM, OBST, GEN>(C.phi, C.mu, C.h, Gs, Js, Cs, tt, c, x, phin, mun, h1);
+        if (valid) store3d<R, NP, NM, GEN, DIAG, NT>(out, g, o0 + (int64_t)m * sz, phin, mun, gy, da, dc);
+        __syncthreads();
+    };
+    for (int m = t.m0; m < t.m1;) {
+        plane(m, A, B);
+        if (++m >= t.m1) break;
+        plane(m, B, A);
+        ++m;
+    }
+}
+
+// The anisotropic step of one block.
+template <typename R, int NP, int NM, bool OBST, int BX, int BY, bool GEN, bool DIAG, bool NT>
+__device__ __forceinline__ void step3d_aniso(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
+                                             const Coef<R>& c, const int64_t* __restrict__ stepctr, int kstep,
+                                             double tb0, double tdn, double tslope, int seg, int ntx, int nty,
+                                             const CoefX<R>* x, DiagAcc* da, const DiagCoef* dc) {
+    constexpr int NF = NP + NM;
+    constexpr int NMM = mob_n<NM, GEN>();
+    typedef Tile3d<BX, BY, true> Tile;
+    constexpr int PW = Tile::PW, PP = Tile::PP, NPOS = Tile::NPOS;
+    __shared__ R sp[4][NP][PP];
+    __shared__ R su[3][NM][PP];
+    __shared__ R sm[3][NMM][PP];
+    Tile t;
+    t.init(g, seg, ntx, nty);
+    const bool perz = g.bcz == MP_BC_PERIODIC;
+    const int64_t sz = (int64_t)g.nx * g.ny;
+    const int64_t fs = g.fstride;
 
     R reg[NPOS][NF];
     auto fetch = [&](int m) {
-        const int64_t mo = (int64_t)gmap(m, g.nz, perz) * sz;
+        const R* p = in + (int64_t)gmap(m, g.nz, perz) * sz;
 #pragma unroll
-        for (int k = 0; k < NPOS; ++k) {
-            if (tid + k * NT < PP) {
+        for (int k = 0; k < NPOS; ++k)
+            if (t.has(k)) {
 #pragma unroll
-                for (int f = 0; f < NF; ++f) reg[k][f] = in[f * fs + mo + poff[k]];
+                for (int f = 0; f < NF; ++f) reg[k][f] = p[f * fs + t.off[k]];
             }
-        }
     };
-    auto stage = [&](int m) {
-        const int sl = (m + NS) & (NS - 1);
+    // phi of plane m into slot m & 3, its mu and M~ into slot su_
+    auto stage = [&](int m, int su_) {
+        const int sl = m & 3;
 #pragma unroll
-        for (int k = 0; k < NPOS; ++k) {
-            const int p = ppos[k];
-            if (tid + k * NT < PP) {
+        for (int k = 0; k < NPOS; ++k)
+            if (t.has(k)) {
                 R ph[NP], hh[NP], Mt[NMM];
 #pragma unroll
-                for (int f = 0; f < NF; ++f) sv[sl][f][p] = reg[k][f];
-#pragma unroll
-                for (int a = 0; a < NP; ++a) ph[a] = reg[k][a];
+                for (int a = 0; a < NP; ++a) {
+                    ph[a] = reg[k][a];
+                    sp[sl][a][t.pos[k]] = ph[a];
+                }
                 interp_h<R, NP>(ph, hh);
                 mobility_any<R, NP, NM, GEN>(hh, c, x, Mt);
 #pragma unroll
-                for (int kk = 0; kk < NMM; ++kk) sm[sl][kk][p] = Mt[kk];
+                for (int kk = 0; kk < NM; ++kk) su[su_][kk][t.pos[k]] = reg[k][NP + kk];
+#pragma unroll
+                for (int kk = 0; kk < NMM; ++kk) sm[su_][kk][t.pos[k]] = Mt[kk];
             }
-        }
     };
 
-    // Face between (sL, pL) and (sR, pR); tangential axes given as (slot, offset)
-    // steps: dS*[t] is the slot step, dP*[t] the in-plane position step.
-    auto face = [&](int sL, int pL, int sR, int pR, const int (&tS)[2], const int (&tP)[2],
-                    R (&U)[NP], R (&Wf)[NP], R (&J)[NM]) {
+    // Face between positions (sL, pL) and (sR, pR) of the phi ring (uL, uR:
+    // slots of mu and M~); tangential axes given as (slot, offset) steps: tS[t]
+    // is the plane step, tP[t] the in-plane position step.
+    auto face = [&](int sL, int uL_, int pL, int sR, int uR_, int pR, const int (&tS)[2], const int (&tP)[2],
+                    R(&U)[NP], R(&Wf)[NP], R(&J)[NM]) {
         R phL[NP], phR[NP], uL[NM], uR[NM], mL[NMM], mR[NMM];
 #pragma unroll
         for (int a = 0; a < NP; ++a) {
-            phL[a] = sv[sL][a][pL];
-            phR[a] = sv[sR][a][pR];
+            phL[a] = sp[sL][a][pL];
+            phR[a] = sp[sR][a][pR];
         }
 #pragma unroll
         for (int k = 0; k < NM; ++k) {
-            uL[k] = sv[sL][NP + k][pL];
-            uR[k] = sv[sR][NP + k][pR];
+            uL[k] = su[uL_][k][pL];
+            uR[k] = su[uR_][k][pR];
         }
 #pragma unroll
         for (int k = 0; k < NMM; ++k) {
-            mL[k] = sm[sL][k][pL];
-            mR[k] = sm[sR][k][pR];
+            mL[k] = sm[uL_][k][pL];
+            mR[k] = sm[uR_][k][pR];
         }
         R tau[2][NP];
-        if constexpr (ANISO) {
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                const int sLp = (sL + tS[t] + NS) & (NS - 1), sLm = (sL - tS[t] + NS) & (NS - 1);
-                const int sRp = (sR + tS[t] + NS) & (NS - 1), sRm = (sR - tS[t] + NS) & (NS - 1);
+        for (int i = 0; i < 2; ++i) {
+            const int sLp = (sL + tS[i]) & 3, sLm = (sL - tS[i]) & 3;
+            const int sRp = (sR + tS[i]) & 3, sRm = (sR - tS[i]) & 3;
 #pragma unroll
-                for (int a = 0; a < NP; ++a)
-                    tau[t][a] = (sv[sLp][a][pL + tP[t]] - sv[sLm][a][pL - tP[t]]) +
-                                (sv[sRp][a][pR + tP[t]] - sv[sRm][a][pR - tP[t]]);
-            }
+            for (int a = 0; a < NP; ++a)
+                tau[i][a] = (sp[sLp][a][pL + tP[i]] - sp[sLm][a][pL - tP[i]]) +
+                            (sp[sRp][a][pR + tP[i]] - sp[sRm][a][pR - tP[i]]);
         }
-        face_core<R, NP, NM, ANISO, 2, GEN>(phL, phR, tau, mL, mR, uL, uR, c, U, Wf, J);
+        face_core<R, NP, NM, true, 2, GEN>(phL, phR, tau, mL, mR, uL, uR, c, U, Wf, J);
     };
 
-    fetch(m0 - 1);
-    stage(m0 - 1);
-    fetch(m0);
-    stage(m0);
-    fetch(m0 + 1);
-    stage(m0 + 1);
+    // slots of mu and M~: of the plane being computed, the next one, and the
+    // one being filled (the prologue puts plane m0 - 1 there; its z face reads
+    // only the thread's own cell of that slot)
+    int ua = 0, ub = 1, uc = 2;
+    fetch(t.m0 - 1);
+    stage(t.m0 - 1, uc);
+    fetch(t.m0);
+    stage(t.m0, ua);
+    fetch(t.m0 + 1);
+    stage(t.m0 + 1, ub);
     __syncthreads();
 
-    const int pc = (ly + 1) * PW + (lx + 1);
-    const int gx = x0 + lx;
-    const int gy = y0 + ly;
+    const int pc = t.pos[0];
+    const int gx = t.x0 + t.tid % BX;
+    const int gy = t.y0 + t.tid / BX;
     const bool valid = gx < g.nx && gy < g.ny;
+    const int64_t o0 = (int64_t)gx + (int64_t)gy * g.nx;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
     R Cs[NP];  // T - Te depends on y only
     const R tt = (R)(tbase + tslope * (double)gy);
@@ -171,20 +360,19 @@ __device__ __forceinline__ void step3d_block(const R* __restrict__ in, R* __rest
     R Wlo[NP], Jlo[NM];  // z face between planes m-1 and m
     {
         R Ud[NP];
-        const int s0 = (m0 + NS) & (NS - 1), sm1 = (m0 - 1 + NS) & (NS - 1);
-        face(sm1, pc, s0, pc, tSz, tPz, Ud, Wlo, Jlo);
+        face((t.m0 - 1) & 3, uc, pc, t.m0 & 3, ua, pc, tSz, tPz, Ud, Wlo, Jlo);
     }
 
-    for (int m = m0; m < m1; ++m) {
-        if (m + 2 <= m1) fetch(m + 2);
-        const int s0 = (m + NS) & (NS - 1);
-        const int sp1 = (m + 1) & (NS - 1);
+    for (int m = t.m0; m < t.m1; ++m) {
+        if (m + 2 <= t.m1) fetch(m + 2);
+        const int s0 = m & 3;
+        const int sp1 = (m + 1) & 3;
 
         R Gs[NP], Js[NM];
         {
             R Ul[NP], Wl[NP], Jl[NM], Uh[NP], Wh[NP], Jh[NM];
-            face(s0, pc - 1, s0, pc, tSx, tPx, Ul, Wl, Jl);
-            face(s0, pc, s0, pc + 1, tSx, tPx, Uh, Wh, Jh);
+            face(s0, ua, pc - 1, s0, ua, pc, tSx, tPx, Ul, Wl, Jl);
+            face(s0, ua, pc, s0, ua, pc + 1, tSx, tPx, Uh, Wh, Jh);
 #pragma unroll
             for (int a = 0; a < NP; ++a) Gs[a] = Uh[a] - Wl[a];
 #pragma unroll
@@ -192,8 +380,8 @@ __device__ __forceinline__ void step3d_block(const R* __restrict__ in, R* __rest
         }
         {
             R Ul[NP], Wl[NP], Jl[NM], Uh[NP], Wh[NP], Jh[NM];
-            face(s0, pc - PW, s0, pc, tSy, tPy, Ul, Wl, Jl);
-            face(s0, pc, s0, pc + PW, tSy, tPy, Uh, Wh, Jh);
+            face(s0, ua, pc - PW, s0, ua, pc, tSy, tPy, Ul, Wl, Jl);
+            face(s0, ua, pc, s0, ua, pc + PW, tSy, tPy, Uh, Wh, Jh);
 #pragma unroll
             for (int a = 0; a < NP; ++a) Gs[a] = Gs[a] + (Uh[a] - Wl[a]);
 #pragma unroll
@@ -201,7 +389,7 @@ __device__ __forceinline__ void step3d_block(const R* __restrict__ in, R* __rest
         }
         {
             R Uh[NP], Wh[NP], Jh[NM];
-            face(s0, pc, sp1, pc, tSz, tPz, Uh, Wh, Jh);
+            face(s0, ua, pc, sp1, ub, pc, tSz, tPz, Uh, Wh, Jh);
 #pragma unroll
             for (int a = 0; a < NP; ++a) {
                 Gs[a] = Gs[a] + (Uh[a] - Wlo[a]);
@@ -216,52 +404,60 @@ __device__ __forceinline__ void step3d_block(const R* __restrict__ in, R* __rest
 
         R phi[NP], mu[NM], h0[NP];
 #pragma unroll
-        for (int a = 0; a < NP; ++a) phi[a] = sv[s0][a][pc];
+        for (int a = 0; a < NP; ++a) phi[a] = sp[s0][a][pc];
 #pragma unroll
-        for (int k = 0; k < NM; ++k) mu[k] = sv[s0][NP + k][pc];
+        for (int k = 0; k < NM; ++k) mu[k] = su[ua][k][pc];
         interp_h<R, NP>(phi, h0);
         R phin[NP], mun[NM];
         R h1[NP];
         cell_update_any<R, NP, NM, OBST, GEN>(phi, mu, h0, Gs, Js, Cs, tt, c, x, phin, mun, h1);
+        if (valid) store3d<R, NP, NM, GEN, DIAG, NT>(out, g, o0 + (int64_t)m * sz, phin, mun, gy, da, dc);
 
-        if (valid) {
-            const int64_t o = (int64_t)gx + (int64_t)gy * sy + (int64_t)m * sz;
-#pragma unroll
-            for (int a = 0; a < NP; ++a) out[a * fs + o] = phin[a];
-#pragma unroll
-            for (int k = 0; k < NM; ++k) out[(NP + k) * fs + o] = mun[k];
-            if constexpr (DIAG) {
-                double p[NP], u[NM];
-#pragma unroll
-                for (int a = 0; a < NP; ++a) p[a] = (double)phin[a];
-#pragma unroll
-                for (int k = 0; k < NM; ++k) u[k] = (double)mun[k];
-                diag_cell<NP, NM, GEN>(p, u, dc->tt0 + dc->tslope * (double)gy, *dc, *da);
-            }
-        }
-
-        if (m + 2 <= m1) stage(m + 2);
+        if (m + 2 <= t.m1) stage(m + 2, uc);
+        const int u = ua;
+        ua = ub;
+        ub = uc;
+        uc = u;
         __syncthreads();
     }
 }
 
-template <typename R, int NP, int NM, bool ANISO, bool OBST, int BX, int BY>
-__global__ void __launch_bounds__(BX * BY)
+template <typename R, int NP, int NM, bool ANISO, bool OBST, int BX, int BY, bool GEN, bool DIAG = false,
+          bool NT = false>
+__device__ __forceinline__ void step3d_block(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
+                                             const Coef<R>& c, const int64_t* __restrict__ stepctr, int kstep,
+                                             double tb0, double tdn, double tslope, int seg, int ntx, int nty,
+                                             const CoefX<R>* x, DiagAcc* da = nullptr,
+                                             const DiagCoef* dc = nullptr) {
+    if constexpr (ANISO)
+        step3d_aniso<R, NP, NM, OBST, BX, BY, GEN, DIAG, NT>(in, out, g, c, stepctr, kstep, tb0, tdn, tslope, seg, ntx,
+                                                         nty, x, da, dc);
+    else
+        step3d_iso<R, NP, NM, OBST, BX, BY, GEN, DIAG, NT>(in, out, g, c, stepctr, kstep, tb0, tdn, tslope, seg, ntx,
+                                                       nty, x, da, dc);
+}
+
+// FP64 at three waves per SIMD: the isotropic kernel of three phases and two mu
+// fields fits them without spills (182 registers otherwise).
+#define MP3_WAVES(R) (sizeof(R) == 8 ? 3 : 2)
+
+template <typename R, int NP, int NM, bool ANISO, bool OBST, int BX, int BY, bool NT>
+__global__ void __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(MP3_WAVES(R))))
 k_step3d(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
          const int64_t* __restrict__ stepctr, int kstep, double tb0, double tdn, double tslope,
          int seg, int ntx, int nty) {
-    step3d_block<R, NP, NM, ANISO, OBST, BX, BY, false>(in, out, g, c, stepctr, kstep, tb0, tdn, tslope, seg,
-                                                        ntx, nty, nullptr);
+    step3d_block<R, NP, NM, ANISO, OBST, BX, BY, false, false, NT>(in, out, g, c, stepctr, kstep, tb0, tdn, tslope,
+                                                                   seg, ntx, nty, nullptr);
 }
 
-// The extended model's 3D kernel (64 x 4 tiles).
+// The extended model's 3D kernel (32 x 8 tiles).
 template <typename R, int NP, int NM, bool ANISO, bool OBST>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MP3_WAVES(R))))
 k_step3d_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
              const int64_t* __restrict__ stepctr, int kstep, double tb0, double tdn, double tslope,
              int seg, int ntx, int nty, CoefX<R> x) {
-    step3d_block<R, NP, NM, ANISO, OBST, 64, 4, true>(in, out, g, c, stepctr, kstep, tb0, tdn, tslope, seg,
-                                                      ntx, nty, &x);
+    step3d_block<R, NP, NM, ANISO, OBST, 32, 8, true>(in, out, g, c, stepctr, kstep, tb0, tdn, tslope, seg, ntx,
+                                                      nty, &x);
 }
 
 // The same tiles writing, beside the state, one partial diagnostics record
@@ -324,8 +520,8 @@ int call_3d_diag(const StepLaunch& L, const Coef<R>& c, const CoefX<R>& x, Kerne
 template <typename R, int NP, int NM, bool ANISO, bool OBST, bool DIAG = false>
 int call_3d_gen(const StepLaunch& L, const Coef<R>& c, const CoefX<R>& x, KernelCall& k) {
     if constexpr (DIAG) return call_3d_diag<R, NP, NM, ANISO, OBST, 4, true>(L, c, x, k);
-    const int ntx = (L.g.nx + 63) / 64;
-    const int nty = (L.g.ny + 3) / 4;
+    const int ntx = (L.g.nx + 31) / 32;
+    const int nty = (L.g.ny + 7) / 8;
     const int nseg = (L.g.nz + L.seg - 1) / L.seg;
     const long long nblocks = (long long)ntx * nty * nseg;
     if (nblocks <= 0 || nblocks > 0x7fffffffLL) return MP_E_PARAM;
@@ -348,15 +544,15 @@ int call_3d_gen(const StepLaunch& L, const Coef<R>& c, const CoefX<R>& x, Kernel
     return MP_OK;
 }
 
-template <typename R, int NP, int NM, bool ANISO, bool OBST, int BY>
+template <typename R, int NP, int NM, bool ANISO, bool OBST, int BX, int BY>
 int call_3d_by(const StepLaunch& L, const Coef<R>& c, KernelCall& k) {
-    constexpr int BX = 64;
     const int ntx = (L.g.nx + BX - 1) / BX;
     const int nty = (L.g.ny + BY - 1) / BY;
     const int nseg = (L.g.nz + L.seg - 1) / L.seg;
     const long long nblocks = (long long)ntx * nty * nseg;
     if (nblocks <= 0 || nblocks > 0x7fffffffLL) return MP_E_PARAM;
-    k.func = (const void*)&k_step3d<R, NP, NM, ANISO, OBST, BX, BY>;
+    k.func = L.nt ? (const void*)&k_step3d<R, NP, NM, ANISO, OBST, BX, BY, true>
+                  : (const void*)&k_step3d<R, NP, NM, ANISO, OBST, BX, BY, false>;
     k.grid = dim3((unsigned)nblocks);
     k.block = dim3(BX * BY);
     k.arg((const R*)L.in);
@@ -374,14 +570,17 @@ int call_3d_by(const StepLaunch& L, const Coef<R>& c, KernelCall& k) {
     return MP_OK;
 }
 
-// LDS bytes of a 64 x BY tile ring (4 planes of the fields and M~, with halo).
+// bx = threads per block: 256 (32 x 8 tiles: a row is one 128-byte line in
+// FP32, and the halo, 1.33 staged cells per cell, is the smallest for the size)
+// or 512 (64 x 8), accepted where four planes of all its records fit in 64 KiB.
+// FP32 512^3 anisotropic: 897 us with 32 x 8 tiles, 913 with 64 x 4, 904 with
+// 64 x 8; FP64 256^3 with three phases 318 / 336 us (32 x 8, 64 x 4). The
+// diagnostics instances take 64 x 4 and 64 x 8.
 template <typename R, int NP, int NM, int BY>
 constexpr int lds3d_bytes() {
     return 4 * (NP + 2 * NM) * 66 * (BY + 2) * (int)sizeof(R);
 }
 
-// bx = threads per block: 256 (64 x 4 tiles) or 512 (64 x 8 tiles, taller, so
-// fewer y-halo rows are loaded per cell; only where the LDS ring stays small).
 template <typename R, int NP, int NM, bool ANISO, bool OBST, bool DIAG = false>
 int call_3d(const StepLaunch& L, const Coef<R>& c, KernelCall& k) {
     if constexpr (DIAG) {
@@ -395,10 +594,10 @@ int call_3d(const StepLaunch& L, const Coef<R>& c, KernelCall& k) {
     } else {
         if (L.bx == 512) {
             if constexpr (lds3d_bytes<R, NP, NM, 8>() <= 64 * 1024)
-                return call_3d_by<R, NP, NM, ANISO, OBST, 8>(L, c, k);
+                return call_3d_by<R, NP, NM, ANISO, OBST, 64, 8>(L, c, k);
             return MP_E_PARAM;
         }
-        return call_3d_by<R, NP, NM, ANISO, OBST, 4>(L, c, k);
+        return call_3d_by<R, NP, NM, ANISO, OBST, 32, 8>(L, c, k);
     }
 }
 
