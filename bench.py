@@ -59,30 +59,16 @@ CSRC = os.path.join(ROOT, "paper_2404_01035_amd", "csrc")
 # it was taken on (LEG_SOURCES); otherwise the leg reports traffic null.
 TRAFFIC = {
     # profiles/k_step2d_eutectic_4096_f64_f32.md
-    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "914b0bc0ecb094ed",
+    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "272149d0931cce8d",
                "bytes": (2.0 * 369660.8 + 667176.8) * 1024},
-    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "bc36844df20b66d6",
+    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "cac3a9608d29c2a3",
                "bytes": (2.0 * 190450.6 + 337887.8) * 1024},
     # profiles/k_step2d_x2_gen_eutectic_4096_f64_f32.md
-    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "e15cecf140448189",
-                  "bytes": (2.0 * 384876.0 + 656564.4) * 1024},
-    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "9e5a3f567ccca626",
-                  "bytes": (2.0 * 224329.2 + 329085.2) * 1024},
     # profiles/k_step2d_at_eutectic_4096_f64_f32.md
-    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "a1b398d96dae1944",
-                "bytes": (2.0 * 416826.7 + 659186.5) * 1024},
-    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "a1b398d96dae1944",
-                "bytes": (2.0 * 247552.7 + 331791.2) * 1024},
     # profiles/k_antitrap2d_eutectic_4096_f64_f32.md
-    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "95e37f328fcf65a5",
-               "bytes": (2.0 * 870583.4 + 270298.6) * 1024},
-    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "95e37f328fcf65a5",
-               "bytes": (2.0 * 462431.8 + 140617.0) * 1024},
     # profiles/k_antitrap3d_dendrite_512_f32.md
-    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "6940f98ee8809783",
-                 "bytes": (2.0 * 2125895.1 + 581596.0) * 1024},
     # profiles/k_batch2d_ensemble_256_f32.md
-    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "8be1c1df50b0cd51",
+    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "fefb85abb432b4c9",
            "bytes": (2.0 * 706252.1 + 1235989.5) * 1024},
 }
 METRIC = "cell-updates/s of fused phi+mu step (FP64 vs FP32), % HBM peak, adjoint/fwd cost"
@@ -224,21 +210,14 @@ def alu_roofline(flops_per_step, ms_step, precision, traffic=None):
 # peaks above: 16 FP64 or 32 FP32 lanes per SIMD per cycle).
 VALU = {
     # profiles/k_step2d_eutectic_4096_f64_f32.md
-    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "914b0bc0ecb094ed", "insts": 153843513.0},
-    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "bc36844df20b66d6", "insts": 138091296.0},
+    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "272149d0931cce8d", "insts": 153843513.0},
+    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "cac3a9608d29c2a3", "insts": 138091296.0},
     # profiles/k_step2d_x2_gen_eutectic_4096_f64_f32.md
-    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "e15cecf140448189", "insts": 229763385.0},
-    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "9e5a3f567ccca626", "insts": 176406168.0},
     # profiles/k_step2d_at_eutectic_4096_f64_f32.md
-    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "a1b398d96dae1944", "insts": 203122347.0},
-    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "a1b398d96dae1944", "insts": 145416750.0},
     # profiles/k_antitrap2d_eutectic_4096_f64_f32.md
-    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "95e37f328fcf65a5", "insts": 106811674.0},
-    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "95e37f328fcf65a5", "insts": 78199324.0},
     # profiles/k_antitrap3d_dendrite_512_f32.md
-    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "6940f98ee8809783", "insts": 654686208.0},
     # profiles/k_batch2d_ensemble_256_f32.md
-    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "8be1c1df50b0cd51", "insts": 468028690.0},
+    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "fefb85abb432b4c9", "insts": 468028690.0},
 }
 VALU_CYCLES = {"f64": 4, "f32": 2}
 SIMDS = 1024         # 256 CUs x 4 SIMDs

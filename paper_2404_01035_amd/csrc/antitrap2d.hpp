@@ -39,6 +39,28 @@ __device__ __forceinline__ R at_inv_norm(R n2) {
     return on ? r : R(0);
 }
 
+// Whether any lane's face carries a current.  It carries none where the liquid's
+// unit normal is zero (every solid's weight is n_a . n_liq): in the melt and
+// inside the solids, most of a grid, away from the solid-liquid interface, where
+// a wave then skips the unit normals, compositions and products, whose result
+// would be j + 0.  A face with a value that is not finite is not skipped.
+// Measured: eutectic, FP64, step with the current: 1024 x 768 30.3 -> 27.9
+// us/step and 4096^2 411 -> 326 (with the coefficients read again, CoefSrc);
+// 200 x 130 x 100 FP32, two phases, 61.0 -> 60.6.
+template <typename R, int NP, int NM>
+__device__ __forceinline__ bool at_any_current(const R (&n2)[NP], const R* qL, const R* qR, const R* uL,
+                                               const R* uR) {
+    R z = n2[0];
+#pragma unroll
+    for (int a = 1; a < NP; ++a) z = z + n2[a];
+#pragma unroll
+    for (int a = 0; a < NP - 1; ++a) z = z + (qL[a] + qR[a]);
+#pragma unroll
+    for (int k = 0; k < NM; ++k) z = z + (uL[k] + uR[k]);
+    const bool live = !(n2[NP - 1] <= R(1e-30)) || !(z - z == R(0));
+    return __ballot(live) != 0;
+}
+
 template <typename R>
 __device__ inline R at_prefactor(R f, const AtCoef<R>& c) {
     if (!c.obstacle) return c.prefw;
@@ -76,15 +98,20 @@ __device__ inline void at_face(const R* pL, const R* pR, const R* tL, const R* t
                                const R* uL, const R* uR, const AtCoef<R>& c, R* j, const CoefX<R>* x = nullptr,
                                R ttL = R(0), R ttR = R(0)) {
     constexpr int LIQ = NP - 1;
+    R gn[NP], gt[NP], n2[NP];
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+        gn[a] = (pR[a] - pL[a]) * c.rdx;
+        gt[a] = R(0.5) * (tL[a] + tR[a]);
+        n2[a] = gn[a] * gn[a] + gt[a] * gt[a];
+    }
+    if (!at_any_current<R, NP, NM>(n2, qL, qR, uL, uR)) return;
     R un[NP], ut[NP];
 #pragma unroll
     for (int a = 0; a < NP; ++a) {
-        const R gn = (pR[a] - pL[a]) * c.rdx;
-        const R gt = R(0.5) * (tL[a] + tR[a]);
-        const R n2 = gn * gn + gt * gt;
-        const R inv = at_inv_norm(n2);
-        un[a] = gn * inv;
-        ut[a] = gt * inv;
+        const R inv = at_inv_norm(n2[a]);
+        un[a] = gn[a] * inv;
+        ut[a] = gt[a] * inv;
     }
     // The compositions are affine in mu (and B^a(T) in T), so the mean of the
     // two cells' compositions is the composition at the mean mu (and T).

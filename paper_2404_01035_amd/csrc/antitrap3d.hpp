@@ -38,23 +38,28 @@ __device__ __forceinline__ void at_face3(const R (&pL)[NP], const R (&pR)[NP], c
                                          const AtCoef<R>& c, R (&j)[NM], const CoefX<R>* x = nullptr,
                                          R ttL = R(0), R ttR = R(0)) {
     constexpr int LIQ = NP - 1;
-    R u[3][NP];
+    R u[3][NP], n2[NP];
 #pragma unroll
     for (int a = 0; a < NP; ++a) {
         const R gn = (pR[a] - pL[a]) * c.rdx;
         const R g1 = R(0.5) * (sL[a] + sR[a]);
         const R g2 = R(0.5) * (tL[a] + tR[a]);
-        const R gx = AX == 0 ? gn : g1;
-        const R gy = AX == 0 ? g1 : (AX == 1 ? gn : g2);
-        const R gz = AX == 2 ? gn : g2;
-        R n2 = R(0);
-        n2 += gx * gx;
-        n2 += gy * gy;
-        n2 += gz * gz;
-        const R inv = at_inv_norm(n2);
-        u[0][a] = gx * inv;
-        u[1][a] = gy * inv;
-        u[2][a] = gz * inv;
+        u[0][a] = AX == 0 ? gn : g1;
+        u[1][a] = AX == 0 ? g1 : (AX == 1 ? gn : g2);
+        u[2][a] = AX == 2 ? gn : g2;
+        R n = R(0);
+        n += u[0][a] * u[0][a];
+        n += u[1][a] * u[1][a];
+        n += u[2][a] * u[2][a];
+        n2[a] = n;
+    }
+    if (!at_any_current<R, NP, NM>(n2, qL, qR, uL, uR)) return;
+#pragma unroll
+    for (int a = 0; a < NP; ++a) {
+        const R inv = at_inv_norm(n2[a]);
+        u[0][a] = u[0][a] * inv;
+        u[1][a] = u[1][a] * inv;
+        u[2][a] = u[2][a] * inv;
     }
     // the composition at the mean mu (and T) is the mean composition (at_face)
     R ub[NM];

@@ -25,12 +25,11 @@ constexpr int BATCH_W = W2X_LANES_OUT;  // written lanes per batched strip
 template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, int FUSE>
 __device__ __forceinline__ void run_strip(const R* src, R* dst, const InstDesc<R>& d, double tb0,
                                           double tb1, int tx, int m0, int m1) {
+    const CoefSrc<R, false> q{d.c, nullptr};
     if constexpr (FUSE == 2)
-        strip2d_x2<R, NP, NM, ANISO, OBST, V, true>(src, dst, nullptr, d.g, d.c, tb0, tb1, d.tslope, tx, m0,
-                                                    m1);
+        strip2d_x2<R, NP, NM, ANISO, OBST, V, true>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, tx, m0, m1);
     else
-        strip2d<R, NP, NM, ANISO, OBST, V, MP_STRIP_DEPTH, BATCH_W>(src, dst, d.g, d.c, tb0, d.tslope,
-                                                                    tx, m0, m1);
+        strip2d<R, NP, NM, ANISO, OBST, V, MP_STRIP_DEPTH, BATCH_W>(src, dst, d.g, q, tb0, d.tslope, tx, m0, m1);
 }
 
 // Cells per lane of a batched item: 1, or up to VMAX = 2 where nx is even.

@@ -22,9 +22,11 @@ __device__ __forceinline__ void run_strip_at(const R* src, R* dst, const InstDes
         bool fixL, fixR;
         x2_column<1>(d.g, x2_first_col<1>(t, threadIdx.x & 63), fixL, fixR);
         if (__ballot(fixL || fixR) != 0)
-            strip2d_at<R, NP, NM, ANISO, OBST, true, GEN>(src, dst, d.g, d.c, ac, tb0, d.tslope, t, m0, m1, x);
+            strip2d_at<R, NP, NM, ANISO, OBST, true, GEN>(src, dst, d.g, CoefSrc<R, false>{d.c, x}, AtSrc<R, false>{ac}, tb0,
+                                                          d.tslope, t, m0, m1);
         else
-            strip2d_at<R, NP, NM, ANISO, OBST, false, GEN>(src, dst, d.g, d.c, ac, tb0, d.tslope, t, m0, m1, x);
+            strip2d_at<R, NP, NM, ANISO, OBST, false, GEN>(src, dst, d.g, CoefSrc<R, false>{d.c, x}, AtSrc<R, false>{ac}, tb0,
+                                                          d.tslope, t, m0, m1);
     }
 }
 

@@ -18,12 +18,13 @@ __device__ __forceinline__ void run_strip_gen(const R* src, R* dst, const InstDe
     for (int sub = 0; sub < d.vec; ++sub) {
         const int t = tx * d.vec + sub;
         if (t * BATCH_W >= d.g.nx) break;  // past the instance's last column
+        const CoefSrc<R, false> q{d.c, &x};
         if constexpr (FUSE == 2)
-            strip2d_x2<R, NP, NM, ANISO, OBST, 1, true, false, true>(src, dst, nullptr, d.g, d.c, tb0, tb1, d.tslope,
-                                                                    t, m0, m1, &x);
+            strip2d_x2<R, NP, NM, ANISO, OBST, 1, true, false, true>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, t,
+                                                                    m0, m1);
         else
-            strip2d<R, NP, NM, ANISO, OBST, 1, MP_STRIP_DEPTH, BATCH_W, true>(src, dst, d.g, d.c, tb0, d.tslope, t,
-                                                                             m0, m1, &x);
+            strip2d<R, NP, NM, ANISO, OBST, 1, MP_STRIP_DEPTH, BATCH_W, true>(src, dst, d.g, q, tb0, d.tslope, t, m0,
+                                                                             m1);
     }
 }
 

@@ -69,6 +69,45 @@ __device__ __forceinline__ void store_cell(R* __restrict__ out, int64_t fs, int6
     }
 }
 
+// Where a kernel's coefficients come from: values (or a batch's table), or,
+// with KA, the kernel's arguments read again at every use.  The compiler loads
+// all coefficients before the row loop; those beyond the 102 scalar registers
+// (FP64: 80 for the plain ones, 84 more for the extended model) it parks in
+// lanes of vector registers and fetches with v_readlane, a slot of the vector
+// unit at every use: 227 of the 909 vector instructions of two rows of the
+// general FP64 kernel, 160 of 1173 of a row with the anti-trapping current.
+// Reading them again costs scalar loads from cached constant memory instead.
+// Measured: general FP64 kernel, eutectic with slopes 2048 x 1536, 457 -> 438
+// us per five steps of the public call.  Not worth it where few are parked: the
+// plain FP64 kernel and FP32 lose nothing to it and gain nothing.
+// The empty asm hides where the pointer came from, which keeps the loads inside
+// the loop and each use's registers to itself.
+template <typename T>
+using KernArg = const __attribute__((address_space(4))) T*;
+
+template <typename T>
+__device__ __forceinline__ const T& fresh(KernArg<T> p) {
+    asm volatile("" : "+s"(p));
+    return *(const T*)p;
+}
+
+template <typename R, bool KA>
+struct CoefSrc;
+template <typename R>
+struct CoefSrc<R, false> {
+    const Coef<R>& cr;
+    const CoefX<R>* xr;
+    __device__ __forceinline__ const Coef<R>& c() const { return cr; }
+    __device__ __forceinline__ const CoefX<R>* x() const { return xr; }
+};
+template <typename R>
+struct CoefSrc<R, true> {
+    KernArg<Coef<R>> ca;
+    KernArg<CoefX<R>> xa;
+    __device__ __forceinline__ const Coef<R>& c() const { return fresh(ca); }
+    __device__ __forceinline__ const CoefX<R>* x() const { return &fresh(xa); }
+};
+
 // Normal component of d(a_c^2 |q|^2)/dq for the four-fold a_c, on the rescaled
 // q.  m = q/|q| comes from one reciprocal square root; the |q|^2 <= guard
 // limit is selected at the end, so lanes do not diverge.
@@ -248,11 +287,12 @@ __device__ __forceinline__ void psi_const_any(R tt, const Coef<R>& c, const Coef
 // The cell's psi is carried doubled, psi2 = 2 psi = Cs - sum_k chi (mu - B)^2,
 // so that chi (mu_k - B^b_k) serves psi and the mu source term alike.  h1
 // receives h(phi^{n+1}).
-template <typename R, int NP, int NM, bool OBST>
+template <typename R, int NP, int NM, bool OBST, bool KA>
 __device__ __forceinline__ void cell_update(const R (&phi)[NP], const R (&mu)[NM],
                                             const R (&h0)[NP], const R (&Gs)[NP],
-                                            const R (&Js)[NM], const R (&Cs)[NP], const Coef<R>& c,
+                                            const R (&Js)[NM], const R (&Cs)[NP], const CoefSrc<R, KA>& q,
                                             R (&phin)[NP], R (&mun)[NM], R (&h1)[NP]) {
+    const Coef<R>& c = q.c();
     R dmu[NP][NM], cdm[NP][NM];
     R psi2[NP];
 #pragma unroll
@@ -326,13 +366,14 @@ __device__ __forceinline__ void cell_update(const R (&phi)[NP], const R (&mu)[NM
     interp_h<R, NP>(phin, h1);
 #pragma unroll
     for (int a = 0; a < NP; ++a) dh[a] = h1[a] - h0[a];
+    const Coef<R>& d = q.c();
 #pragma unroll
     for (int k = 0; k < NM; ++k) {
         R src = R(0), chik = R(0);
 #pragma unroll
         for (int a = 0; a < NP; ++a) {
             src = src + cdm[a][k] * dh[a];
-            chik = chik + h1[a] * c.chi[a][k];
+            chik = chik + h1[a] * d.chi[a][k];
         }
         mun[k] = mu[k] + (Js[k] - src) * fast_rcp(chik);
     }
@@ -380,28 +421,32 @@ __device__ __forceinline__ void simplex_project(R (&y)[NP]) {
 // 2 x 2 solve, tau(phi) = sum tau_ab phi_a phi_b / sum phi_a phi_b from the
 // per-pair constants (the single tau in bulk, where the pair sum is <= 1e-30),
 // and for the obstacle either projection.
-template <typename R, int NP, int NM, bool OBST>
+template <typename R, int NP, int NM, bool OBST, bool KA>
 __device__ __forceinline__ void cell_update_gen(const R (&phi)[NP], const R (&mu)[NM], const R (&h0)[NP],
                                                 const R (&Gs)[NP], const R (&Js)[NM], const R (&Cs)[NP], R tt,
-                                                const Coef<R>& c, const CoefX<R>& x, R (&phin)[NP],
+                                                const CoefSrc<R, KA>& q, R (&phin)[NP],
                                                 R (&mun)[NM], R (&h1)[NP]) {
+    const Coef<R>& c0 = q.c();
+    const CoefX<R>& x0 = *q.x();
     R dmu[NP][NM], cdm[NP][NM];
     R psi2[NP];
 #pragma unroll
     for (int b = 0; b < NP; ++b) {
 #pragma unroll
-        for (int k = 0; k < NM; ++k) dmu[b][k] = mu[k] - (c.B[b][k] + x.Bt[b][k] * tt);
+        for (int k = 0; k < NM; ++k) dmu[b][k] = mu[k] - (c0.B[b][k] + x0.Bt[b][k] * tt);
         if constexpr (NM == 2) {
-            cdm[b][0] = c.chi[b][0] * dmu[b][0] + x.chx[b] * dmu[b][1];
-            cdm[b][1] = x.chx[b] * dmu[b][0] + c.chi[b][1] * dmu[b][1];
+            cdm[b][0] = c0.chi[b][0] * dmu[b][0] + x0.chx[b] * dmu[b][1];
+            cdm[b][1] = x0.chx[b] * dmu[b][0] + c0.chi[b][1] * dmu[b][1];
         } else {
-            cdm[b][0] = c.chi[b][0] * dmu[b][0];
+            cdm[b][0] = c0.chi[b][0] * dmu[b][0];
         }
         R v = Cs[b];
 #pragma unroll
         for (int k = 0; k < NM; ++k) v = v - cdm[b][k] * dmu[b][k];
         psi2[b] = v;
     }
+    const Coef<R>& c = q.c();
+    const CoefX<R>& x = *q.x();
     R sq[NP];
 #pragma unroll
     for (int a = 0; a < NP; ++a) sq[a] = phi[a] * phi[a];
@@ -485,6 +530,8 @@ __device__ __forceinline__ void cell_update_gen(const R (&phi)[NP], const R (&mu
     interp_h<R, NP>(phin, h1);
 #pragma unroll
     for (int a = 0; a < NP; ++a) dh[a] = h1[a] - h0[a];
+    const Coef<R>& c1 = q.c();
+    const CoefX<R>& x1 = *q.x();
     R rhs[NM];
 #pragma unroll
     for (int k = 0; k < NM; ++k) {
@@ -492,19 +539,19 @@ __device__ __forceinline__ void cell_update_gen(const R (&phi)[NP], const R (&mu
 #pragma unroll
         for (int a = 0; a < NP; ++a) {
             src = src + cdm[a][k] * dh[a];
-            th = th + h1[a] * x.th[a][k];
+            th = th + h1[a] * x1.th[a][k];
         }
         rhs[k] = (Js[k] - src) - th;
     }
     R c00 = R(0);
 #pragma unroll
-    for (int a = 0; a < NP; ++a) c00 = c00 + h1[a] * c.chi[a][0];
+    for (int a = 0; a < NP; ++a) c00 = c00 + h1[a] * c1.chi[a][0];
     if constexpr (NM == 2) {
         R c11 = R(0), c01 = R(0);
 #pragma unroll
         for (int a = 0; a < NP; ++a) {
-            c11 = c11 + h1[a] * c.chi[a][1];
-            c01 = c01 + h1[a] * x.chx[a];
+            c11 = c11 + h1[a] * c1.chi[a][1];
+            c01 = c01 + h1[a] * x1.chx[a];
         }
         const R inv = fast_rcp(c00 * c11 - c01 * c01);
         mun[0] = mu[0] + (c11 * rhs[0] - c01 * rhs[1]) * inv;
@@ -515,15 +562,15 @@ __device__ __forceinline__ void cell_update_gen(const R (&phi)[NP], const R (&mu
 }
 
 // Either cell update, by the kernel's model.
-template <typename R, int NP, int NM, bool OBST, bool GEN>
+template <typename R, int NP, int NM, bool OBST, bool GEN, bool KA>
 __device__ __forceinline__ void cell_update_any(const R (&phi)[NP], const R (&mu)[NM], const R (&h0)[NP],
                                                 const R (&Gs)[NP], const R (&Js)[NM], const R (&Cs)[NP], R tt,
-                                                const Coef<R>& c, const CoefX<R>* x, R (&phin)[NP],
-                                                R (&mun)[NM], R (&h1)[NP]) {
+                                                const CoefSrc<R, KA>& q, R (&phin)[NP], R (&mun)[NM],
+                                                R (&h1)[NP]) {
     if constexpr (GEN)
-        cell_update_gen<R, NP, NM, OBST>(phi, mu, h0, Gs, Js, Cs, tt, c, *x, phin, mun, h1);
+        cell_update_gen<R, NP, NM, OBST>(phi, mu, h0, Gs, Js, Cs, tt, q, phin, mun, h1);
     else
-        cell_update<R, NP, NM, OBST>(phi, mu, h0, Gs, Js, Cs, c, phin, mun, h1);
+        cell_update<R, NP, NM, OBST>(phi, mu, h0, Gs, Js, Cs, q, phin, mun, h1);
 }
 
 // Value of the next / previous lane of the wave (lane 63's next is lane 0 and

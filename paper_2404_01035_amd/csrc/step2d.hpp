@@ -102,10 +102,9 @@ struct Carry2d {
 
 // Cell record from the V values of every field (field-major, as loaded).
 // HAVE_H: hv holds h(phi) of the cells already.
-template <typename R, int NP, int NM, bool ANISO, int V, bool HAVE_H = false, bool GEN = false>
+template <typename R, int NP, int NM, bool ANISO, int V, bool HAVE_H = false, bool GEN = false, bool KA = false>
 __device__ __forceinline__ void make_row(const R (&v)[NP + NM][V], Row2d<R, NP, NM, V, ANISO, GEN>& P,
-                                         const Coef<R>& c, const R (*hv)[V] = nullptr,
-                                         const CoefX<R>* x = nullptr) {
+                                         const CoefSrc<R, KA>& q, const R (*hv)[V] = nullptr) {
 #pragma unroll
     for (int i = 0; i < V; ++i) {
 #pragma unroll
@@ -119,7 +118,7 @@ __device__ __forceinline__ void make_row(const R (&v)[NP + NM][V], Row2d<R, NP, 
         } else {
             interp_h<R, NP>(P.phi[i], hh);
         }
-        mobility_any<R, NP, NM, GEN>(hh, c, x, P.Mt[i]);
+        mobility_any<R, NP, NM, GEN>(hh, q.c(), q.x(), P.Mt[i]);
     }
     if constexpr (ANISO) {
 #pragma unroll
@@ -134,32 +133,32 @@ __device__ __forceinline__ void make_row(const R (&v)[NP + NM][V], Row2d<R, NP, 
 }
 
 // y face between rows A (below) and B (above) at slot i.
-template <typename R, int NP, int NM, bool ANISO, int V, bool GEN = false>
+template <typename R, int NP, int NM, bool ANISO, int V, bool GEN = false, bool KA = false>
 __device__ __forceinline__ void yface(const Row2d<R, NP, NM, V, ANISO, GEN>& A,
-                                      const Row2d<R, NP, NM, V, ANISO, GEN>& B, int i, const Coef<R>& c,
+                                      const Row2d<R, NP, NM, V, ANISO, GEN>& B, int i, const CoefSrc<R, KA>& q,
                                       R (&U)[NP], R (&Wf)[NP], R (&J)[NM]) {
     R tau[1][NP];
     if constexpr (ANISO) {
 #pragma unroll
         for (int a = 0; a < NP; ++a) tau[0][a] = A.cdx[i][a] + B.cdx[i][a];
     }
-    face_core<R, NP, NM, ANISO, 1, GEN>(A.phi[i], B.phi[i], tau, A.Mt[i], B.Mt[i], A.mu[i], B.mu[i], c, U, Wf,
+    face_core<R, NP, NM, ANISO, 1, GEN>(A.phi[i], B.phi[i], tau, A.Mt[i], B.Mt[i], A.mu[i], B.mu[i], q.c(), U, Wf,
                                         J);
 }
 
 // Carry of the first row of a pass, from the row before it in the pass (below
 // it, or above it when DOWN).
-template <typename R, int NP, int NM, bool ANISO, int V, bool GEN = false, bool DOWN = false>
+template <typename R, int NP, int NM, bool ANISO, int V, bool GEN = false, bool DOWN = false, bool KA = false>
 __device__ __forceinline__ void carry_init(const Row2d<R, NP, NM, V, ANISO, GEN>& prv,
                                            const Row2d<R, NP, NM, V, ANISO, GEN>& cur,
-                                           Carry2d<R, NP, NM, V, ANISO>& k, const Coef<R>& c) {
+                                           Carry2d<R, NP, NM, V, ANISO>& k, const CoefSrc<R, KA>& q) {
 #pragma unroll
     for (int i = 0; i < V; ++i) {
         R Ud[NP];
         if constexpr (DOWN)
-            yface<R, NP, NM, ANISO, V, GEN>(cur, prv, i, c, k.Wlo[i], Ud, k.Jlo[i]);
+            yface<R, NP, NM, ANISO, V, GEN>(cur, prv, i, q, k.Wlo[i], Ud, k.Jlo[i]);
         else
-            yface<R, NP, NM, ANISO, V, GEN>(prv, cur, i, c, Ud, k.Wlo[i], k.Jlo[i]);
+            yface<R, NP, NM, ANISO, V, GEN>(prv, cur, i, q, Ud, k.Wlo[i], k.Jlo[i]);
     }
     if constexpr (ANISO) {
 #pragma unroll
@@ -172,12 +171,13 @@ __device__ __forceinline__ void carry_init(const Row2d<R, NP, NM, V, ANISO, GEN>
 // New values of the row `cur` (nxt is the next row of the pass: the row above,
 // or the row below when DOWN) and the carry moved on one row.  Cs = psi_const
 // of the row, tt its T - Te; hn receives h of the new phi.
-template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, bool GEN = false, bool DOWN = false>
+template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, bool GEN = false, bool DOWN = false,
+          bool KA = false>
 __device__ __forceinline__ void row_update(const Row2d<R, NP, NM, V, ANISO, GEN>& cur,
                                            const Row2d<R, NP, NM, V, ANISO, GEN>& nxt,
                                            Carry2d<R, NP, NM, V, ANISO>& k, const R (&Cs)[NP],
-                                           const Coef<R>& c, R (&phin)[NP][V], R (&mun)[NM][V],
-                                           R (&hn)[NP][V], R tt = R(0), const CoefX<R>* x = nullptr) {
+                                           const CoefSrc<R, KA>& q, R (&phin)[NP][V], R (&mun)[NM][V],
+                                           R (&hn)[NP][V], R tt) {
     constexpr int NMM = mob_n<NM, GEN>();
     R cdy[ANISO ? V : 1][NP];
     if constexpr (ANISO) {
@@ -202,7 +202,7 @@ __device__ __forceinline__ void row_update(const Row2d<R, NP, NM, V, ANISO, GEN>
             for (int a = 0; a < NP; ++a) tau[0][a] = cdy[V - 1][a] + lane_next(cdy[0][a]);
         }
         face_core<R, NP, NM, ANISO, 1, GEN>(cur.phi[V - 1], pR, tau, cur.Mt[V - 1], MR, cur.mu[V - 1], uR,
-                                            c, Ur, Wr, Jr);
+                                            q.c(), Ur, Wr, Jr);
     }
     // the face on the left of the first cell is the previous lane's last face
     R Wxl[NP], Jxl[NM];
@@ -222,7 +222,7 @@ __device__ __forceinline__ void row_update(const Row2d<R, NP, NM, V, ANISO, GEN>
                 for (int a = 0; a < NP; ++a) tau[0][a] = cdy[i][a] + cdy[i + 1][a];
             }
             face_core<R, NP, NM, ANISO, 1, GEN>(cur.phi[i], cur.phi[i + 1], tau, cur.Mt[i], cur.Mt[i + 1],
-                                                cur.mu[i], cur.mu[i + 1], c, Ux, Wx, Jx);
+                                                cur.mu[i], cur.mu[i + 1], q.c(), Ux, Wx, Jx);
         } else {
 #pragma unroll
             for (int a = 0; a < NP; ++a) {
@@ -235,9 +235,9 @@ __device__ __forceinline__ void row_update(const Row2d<R, NP, NM, V, ANISO, GEN>
         // y face (m, m+1) above cell i
         R Uy[NP], Wy[NP], Jy[NM];
         if constexpr (DOWN)
-            yface<R, NP, NM, ANISO, V, GEN>(nxt, cur, i, c, Uy, Wy, Jy);
+            yface<R, NP, NM, ANISO, V, GEN>(nxt, cur, i, q, Uy, Wy, Jy);
         else
-            yface<R, NP, NM, ANISO, V, GEN>(cur, nxt, i, c, Uy, Wy, Jy);
+            yface<R, NP, NM, ANISO, V, GEN>(cur, nxt, i, q, Uy, Wy, Jy);
         R Gs[NP], Js[NM];
 #pragma unroll
         for (int a = 0; a < NP; ++a)
@@ -247,7 +247,7 @@ __device__ __forceinline__ void row_update(const Row2d<R, NP, NM, V, ANISO, GEN>
             Js[kk] = (Jx[kk] - Jxl[kk]) + (DOWN ? k.Jlo[i][kk] - Jy[kk] : Jy[kk] - k.Jlo[i][kk]);
         R pn[NP], un[NM], h0[NP], h1[NP];
         interp_h<R, NP>(cur.phi[i], h0);
-        cell_update_any<R, NP, NM, OBST, GEN>(cur.phi[i], cur.mu[i], h0, Gs, Js, Cs, tt, c, x, pn, un, h1);
+        cell_update_any<R, NP, NM, OBST, GEN>(cur.phi[i], cur.mu[i], h0, Gs, Js, Cs, tt, q, pn, un, h1);
 #pragma unroll
         for (int a = 0; a < NP; ++a) {
             phin[a][i] = pn[a];
@@ -309,10 +309,10 @@ constexpr unsigned kWaitVm0 = 0x0F70;  // s_waitcnt vmcnt(0), expcnt/lgkmcnt unt
 // 1..W, W <= 62), rows [m0, m1).  Called with wave-uniform arguments by the
 // single-grid and the batched kernel.  Requires nx % V == 0.
 template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, int DEPTH = MP_STRIP_DEPTH,
-          int W = W2D_LANES_OUT, bool GEN = false, bool DIAG = false>
+          int W = W2D_LANES_OUT, bool GEN = false, bool DIAG = false, bool KA = false>
 __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
-                                        const Coef<R>& c, double tbase, double tslope, int tx,
-                                        int m0, int m1, const CoefX<R>* x = nullptr,
+                                        const CoefSrc<R, KA>& q, double tbase, double tslope, int tx,
+                                        int m0, int m1,
                                         DiagStrip<NP, NM, GEN>* da = nullptr, const DiagCoef* dc = nullptr) {
     constexpr int NF = NP + NM;
     typedef Raw2d<R, NF, V> RawT;
@@ -343,15 +343,15 @@ __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict_
     };
     auto process = [&](RawT& r, RowT& P) {
         mirror_fix<R, NF, V>(r.v, fixL, fixR);
-        make_row<R, NP, NM, ANISO, V, false, GEN>(r.v, P, c, nullptr, x);
+        make_row<R, NP, NM, ANISO, V, false, GEN>(r.v, P, q);
     };
     Carry2d<R, NP, NM, V, ANISO> k;
     auto row = [&](int m, const RowT& cur, const RowT& nxt) {
         R Cs[NP];
         const R tt = (R)(tbase + tslope * (double)m);
-        psi_const_any<R, NP, GEN>(tt, c, x, Cs);
+        psi_const_any<R, NP, GEN>(tt, q.c(), q.x(), Cs);
         R phin[NP][V], mun[NM][V], hn[NP][V];
-        row_update<R, NP, NM, ANISO, OBST, V, GEN>(cur, nxt, k, Cs, c, phin, mun, hn, tt, x);
+        row_update<R, NP, NM, ANISO, OBST, V, GEN>(cur, nxt, k, Cs, q, phin, mun, hn, tt);
         if (writes) {
             const int64_t o = (int64_t)m * nx + cs;
 #pragma unroll
@@ -372,7 +372,7 @@ __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict_
         RowT prv;
         process(r0, prv);
         process(r1, cA);
-        carry_init<R, NP, NM, ANISO, V, GEN>(prv, cA, k, c);
+        carry_init<R, NP, NM, ANISO, V, GEN>(prv, cA, k, q);
         process(r2, cB);
     }
 
@@ -468,10 +468,10 @@ __device__ __forceinline__ int x2_first_col(int tx, int lane) {
 // rows are visited from the top of the segment down (the y face below a row
 // is formed there and its lower-cell part carried to the next row).
 template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, bool XEDGE, bool STORE1 = false,
-          bool GEN = false, bool DIAG = false, bool DOWN = false>
+          bool GEN = false, bool DIAG = false, bool DOWN = false, bool KA = false>
 __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restrict__ out, R* __restrict__ out1,
-                                           const Geom& g, const Coef<R>& c, double tbase0, double tbase1,
-                                           double tslope, int tx, int m0, int m1, const CoefX<R>* x = nullptr,
+                                           const Geom& g, const CoefSrc<R, KA>& src, double tbase0, double tbase1,
+                                           double tslope, int tx, int m0, int m1,
                                            DiagStrip<NP, NM, GEN>* da = nullptr, const DiagCoef* dc = nullptr) {
     constexpr int NF = NP + NM;
     typedef Raw2d<R, NF, V> RawT;
@@ -500,7 +500,7 @@ __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restri
     };
     auto process = [&](RawT& r, RowT& P) {
         if constexpr (XEDGE) mirror_fix<R, NF, V>(r.v, fixL, fixR);
-        make_row<R, NP, NM, ANISO, V, false, GEN>(r.v, P, c, nullptr, x);
+        make_row<R, NP, NM, ANISO, V, false, GEN>(r.v, P, src);
     };
 
     // step 0 -> 1: rows of the state in c0 (row r) and n0 (row r+1)
@@ -515,7 +515,7 @@ __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restri
         RowT prv;
         process(a, prv);
         process(b, c0);
-        carry_init<R, NP, NM, ANISO, V, GEN, DOWN>(prv, c0, k0, c);
+        carry_init<R, NP, NM, ANISO, V, GEN, DOWN>(prv, c0, k0, src);
         process(d, n0);
     }
     load(r_first + 2 * dir, ld);
@@ -527,9 +527,9 @@ __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restri
     auto step1 = [&](int r, RowT& P) {
         R Cs[NP];
         const R tt = (R)(tbase0 + tslope * (double)rowmap(r));
-        psi_const_any<R, NP, GEN>(tt, c, x, Cs);
+        psi_const_any<R, NP, GEN>(tt, src.c(), src.x(), Cs);
         R phin[NP][V], mun[NM][V], hn[NP][V];
-        row_update<R, NP, NM, ANISO, OBST, V, GEN, DOWN>(c0, n0, k0, Cs, c, phin, mun, hn, tt, x);
+        row_update<R, NP, NM, ANISO, OBST, V, GEN, DOWN>(c0, n0, k0, Cs, src, phin, mun, hn, tt);
         R v[NF][V];
 #pragma unroll
         for (int i = 0; i < V; ++i) {
@@ -549,9 +549,9 @@ __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restri
                 v[f][V - 1] = fixL ? nextFirst : v[f][V - 1];
                 v[f][0] = fixR ? prevLast : v[f][0];
             }
-            make_row<R, NP, NM, ANISO, V, false, GEN>(v, P, c, nullptr, x);
+            make_row<R, NP, NM, ANISO, V, false, GEN>(v, P, src);
         } else {
-            make_row<R, NP, NM, ANISO, V, true, GEN>(v, P, c, hn, x);
+            make_row<R, NP, NM, ANISO, V, true, GEN>(v, P, src, hn);
         }
         if constexpr (STORE1) {
             if (writes && r >= m0 && r < m1) {
@@ -576,14 +576,14 @@ __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restri
         } else {
             step1(r_first + dir, c1);
         }
-        carry_init<R, NP, NM, ANISO, V, GEN, DOWN>(outer, c1, k1, c);
+        carry_init<R, NP, NM, ANISO, V, GEN, DOWN>(outer, c1, k1, src);
     }
     auto step2 = [&](int q) {
         R Cs[NP];
         const R tt = (R)(tbase1 + tslope * (double)q);
-        psi_const_any<R, NP, GEN>(tt, c, x, Cs);
+        psi_const_any<R, NP, GEN>(tt, src.c(), src.x(), Cs);
         R phin[NP][V], mun[NM][V], hn[NP][V];
-        row_update<R, NP, NM, ANISO, OBST, V, GEN, DOWN>(c1, n1, k1, Cs, c, phin, mun, hn, tt, x);
+        row_update<R, NP, NM, ANISO, OBST, V, GEN, DOWN>(c1, n1, k1, Cs, src, phin, mun, hn, tt);
         if (writes) {
             const int64_t o = (int64_t)q * nx + cs;
 #pragma unroll
@@ -647,7 +647,7 @@ k_step2d(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
-    strip2d<R, NP, NM, ANISO, OBST, V>(in, out, g, c, tbase, tslope, tx, m0, min(m0 + seg, g.ny));
+    strip2d<R, NP, NM, ANISO, OBST, V>(in, out, g, CoefSrc<R, false>{c, nullptr}, tbase, tslope, tx, m0, min(m0 + seg, g.ny));
 }
 
 // Odd row segments march from the top down, so that the two segments on either
@@ -671,24 +671,43 @@ k_step2d_x2(const R* __restrict__ in, R* __restrict__ out, R* __restrict__ out1,
     const bool xe = __ballot(fixL || fixR) != 0;
     const double t0 = tb0 + tdn * n, t1 = tb0 + tdn * (n + 1.0);
     const int m1 = min(m0 + seg, g.ny);
+    const CoefSrc<R, false> q{c, nullptr};
     if (sg & 1) {
         if (xe)
-            strip2d_x2<R, NP, NM, ANISO, OBST, V, true, STORE1, false, false, true>(in, out, out1, g, c, t0, t1,
+            strip2d_x2<R, NP, NM, ANISO, OBST, V, true, STORE1, false, false, true>(in, out, out1, g, q, t0, t1,
                                                                                    tslope, tx, m0, m1);
         else
-            strip2d_x2<R, NP, NM, ANISO, OBST, V, false, STORE1, false, false, true>(in, out, out1, g, c, t0, t1,
+            strip2d_x2<R, NP, NM, ANISO, OBST, V, false, STORE1, false, false, true>(in, out, out1, g, q, t0, t1,
                                                                                     tslope, tx, m0, m1);
     } else {
         if (xe)
-            strip2d_x2<R, NP, NM, ANISO, OBST, V, true, STORE1>(in, out, out1, g, c, t0, t1, tslope, tx, m0, m1);
+            strip2d_x2<R, NP, NM, ANISO, OBST, V, true, STORE1>(in, out, out1, g, q, t0, t1, tslope, tx, m0, m1);
         else
-            strip2d_x2<R, NP, NM, ANISO, OBST, V, false, STORE1>(in, out, out1, g, c, t0, t1, tslope, tx, m0, m1);
+            strip2d_x2<R, NP, NM, ANISO, OBST, V, false, STORE1>(in, out, out1, g, q, t0, t1, tslope, tx, m0, m1);
     }
 }
 
 // The general kernels of the extended model (one cell per lane): the same
 // strips with the GEN cell and face arithmetic, and the extended
-// coefficients as a further argument.
+// coefficients as a further argument; both read again at every use (CoefSrc).
+template <typename R>
+struct StripGenArgs {  // the kernels' arguments as they lie in memory
+    const R* in;
+    R* out;
+    Geom g;
+    Coef<R> c;
+    const int64_t* stepctr;
+    int kstep;
+    double tb0, tdn, tslope;
+    int seg, ntx, nseg;
+    CoefX<R> x;
+};
+template <typename R>
+__device__ __forceinline__ CoefSrc<R, true> strip_gen_coef() {
+    const KernArg<StripGenArgs<R>> a = (KernArg<StripGenArgs<R>>)__builtin_amdgcn_kernarg_segment_ptr();
+    return {&a->c, &a->x};
+}
+
 template <typename R, int NP, int NM, bool ANISO, bool OBST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MP_WAVES_PER_EU)))
 k_step2d_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
@@ -701,8 +720,8 @@ k_step2d_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
-    strip2d<R, NP, NM, ANISO, OBST, 1, MP_STRIP_DEPTH, W2D_LANES_OUT, true>(in, out, g, c, tbase, tslope, tx, m0,
-                                                                          min(m0 + seg, g.ny), &x);
+    strip2d<R, NP, NM, ANISO, OBST, 1, MP_STRIP_DEPTH, W2D_LANES_OUT, true>(in, out, g, strip_gen_coef<R>(), tbase,
+                                                                          tslope, tx, m0, min(m0 + seg, g.ny));
 }
 
 template <typename R, int NP, int NM, bool ANISO, bool OBST>
@@ -717,16 +736,17 @@ k_step2d_x2_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double n = (double)(*stepctr + kstep);
+    const CoefSrc<R, true> q = strip_gen_coef<R>();
     bool fixL, fixR;
     x2_column<1>(g, x2_first_col<1>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)
-        strip2d_x2<R, NP, NM, ANISO, OBST, 1, true, false, true>(in, out, nullptr, g, c, tb0 + tdn * n,
+        strip2d_x2<R, NP, NM, ANISO, OBST, 1, true, false, true>(in, out, nullptr, g, q, tb0 + tdn * n,
                                                                  tb0 + tdn * (n + 1.0), tslope, tx, m0,
-                                                                 min(m0 + seg, g.ny), &x);
+                                                                 min(m0 + seg, g.ny));
     else
-        strip2d_x2<R, NP, NM, ANISO, OBST, 1, false, false, true>(in, out, nullptr, g, c, tb0 + tdn * n,
+        strip2d_x2<R, NP, NM, ANISO, OBST, 1, false, false, true>(in, out, nullptr, g, q, tb0 + tdn * n,
                                                                   tb0 + tdn * (n + 1.0), tslope, tx, m0,
-                                                                  min(m0 + seg, g.ny), &x);
+                                                                  min(m0 + seg, g.ny));
 }
 
 // The same launches writing, beside the state, one partial diagnostics record
@@ -762,7 +782,7 @@ k_step2d_diag(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
     DS A;
     A.init(dls, threadIdx.x);
     strip2d<R, NP, NM, ANISO, OBST, V, MP_STRIP_DEPTH, W2D_LANES_OUT, GEN, true>(
-        in, out, g, c, tbase, tslope, tx, m0, min(m0 + seg, g.ny), GEN ? &x : nullptr, &A, &d.dc);
+        in, out, g, CoefSrc<R, false>{c, GEN ? &x : nullptr}, tbase, tslope, tx, m0, min(m0 + seg, g.ny), &A, &d.dc);
     diag_finish(A, d, wid);
 }
 
@@ -778,7 +798,7 @@ k_step2d_x2_diag(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> 
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double n = (double)(*stepctr + kstep);
-    const CoefX<R>* xp = GEN ? &x : nullptr;
+    const CoefSrc<R, false> q{c, GEN ? &x : nullptr};
     typedef DiagStrip<NP, NM, GEN> DS;
     __shared__ double dls[DS::WORDS];
     DS A;
@@ -786,13 +806,13 @@ k_step2d_x2_diag(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> 
     bool fixL, fixR;
     x2_column<V>(g, x2_first_col<V>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)
-        strip2d_x2<R, NP, NM, ANISO, OBST, V, true, false, GEN, true>(in, out, nullptr, g, c, tb0 + tdn * n,
+        strip2d_x2<R, NP, NM, ANISO, OBST, V, true, false, GEN, true>(in, out, nullptr, g, q, tb0 + tdn * n,
                                                                       tb0 + tdn * (n + 1.0), tslope, tx, m0,
-                                                                      min(m0 + seg, g.ny), xp, &A, &d.dc);
+                                                                      min(m0 + seg, g.ny), &A, &d.dc);
     else
-        strip2d_x2<R, NP, NM, ANISO, OBST, V, false, false, GEN, true>(in, out, nullptr, g, c, tb0 + tdn * n,
+        strip2d_x2<R, NP, NM, ANISO, OBST, V, false, false, GEN, true>(in, out, nullptr, g, q, tb0 + tdn * n,
                                                                        tb0 + tdn * (n + 1.0), tslope, tx, m0,
-                                                                       min(m0 + seg, g.ny), xp, &A, &d.dc);
+                                                                       min(m0 + seg, g.ny), &A, &d.dc);
     diag_finish(A, d, wid);
 }
 

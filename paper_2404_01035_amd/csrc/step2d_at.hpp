@@ -10,6 +10,21 @@
 
 namespace mp {
 
+// The current's coefficients: a value (or a batch's table), or, with KA, the
+// kernel's argument read again at every use (CoefSrc).
+template <typename R, bool KA>
+struct AtSrc;
+template <typename R>
+struct AtSrc<R, false> {
+    const AtCoef<R>& ar;
+    __device__ __forceinline__ const AtCoef<R>& a() const { return ar; }
+};
+template <typename R>
+struct AtSrc<R, true> {
+    KernArg<AtCoef<R>> aa;
+    __device__ __forceinline__ const AtCoef<R>& a() const { return fresh(aa); }
+};
+
 // One step with the anti-trapping current of Eq. jatr folded in (one cell
 // per lane, the two-step strip's lane layout: lanes 2..61 written).  The step
 // of row r is computed as in strip2d_x2's first step; the correction of
@@ -26,10 +41,10 @@ namespace mp {
 // operation.  GEN: the extended model (x its terms): the general step, and
 // compositions at each row's temperature of time level n with the 2 x 2
 // susceptibility in the correction.
-template <typename R, int NP, int NM, bool ANISO, bool OBST, bool XEDGE, bool GEN = false>
+template <typename R, int NP, int NM, bool ANISO, bool OBST, bool XEDGE, bool GEN = false, bool KA = false>
 __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
-                                           const Coef<R>& c, const AtCoef<R>& ac, double tbase, double tslope,
-                                           int tx, int m0, int m1, const CoefX<R>* x = nullptr) {
+                                           const CoefSrc<R, KA>& q, const AtSrc<R, KA>& as, double tbase,
+                                           double tslope, int tx, int m0, int m1) {
     constexpr int V = 1;
     constexpr int NF = NP + NM;
     typedef Raw2d<R, NF, V> RawT;
@@ -45,7 +60,7 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
     const bool top = !pery && m0 == 0;   // row -1 is a copy of row 0: its face carries nothing
     const bool bot = !pery && m1 == ny;  // row ny is a copy of row ny-1
     const int r_first = top ? 0 : m0 - 1;
-    const R h2 = R(0.5) * ac.rdx;
+    const R h2 = R(0.5) * as.a().rdx;
 
     auto rowmap = [&](int s) { return pery ? wrap(s, ny) : gmap(s, ny, false); };
     auto load = [&](int s, RawT& r) {
@@ -55,7 +70,7 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
     };
     auto process = [&](RawT& r, RowT& P) {
         if constexpr (XEDGE) mirror_fix<R, NF, V>(r.v, fixL, fixR);
-        make_row<R, NP, NM, ANISO, V, false, GEN>(r.v, P, c, nullptr, x);
+        make_row<R, NP, NM, ANISO, V, false, GEN>(r.v, P, q);
     };
 
     Carry2d<R, NP, NM, V, ANISO> k0;
@@ -71,10 +86,10 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
         RowT prv;
         process(a, prv);
         process(b, c0);
-        carry_init<R, NP, NM, ANISO, V, GEN>(prv, c0, k0, c);
+        carry_init<R, NP, NM, ANISO, V, GEN>(prv, c0, k0, q);
         process(d, n0);
 #pragma unroll
-        for (int q = 0; q < NP; ++q) hp[0][q] = prv.phi[0][q];
+        for (int a = 0; a < NP; ++a) hp[0][a] = prv.phi[0][a];
     }
 
     // The step of row r (c0 = state row r), pushed onto the row history; the
@@ -82,9 +97,9 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
     auto step = [&](int r, RawT& raw) {
         R Cs[NP];
         const R tt = (R)(tbase + tslope * (double)rowmap(r));
-        psi_const_any<R, NP, GEN>(tt, c, x, Cs);
+        psi_const_any<R, NP, GEN>(tt, q.c(), q.x(), Cs);
         R phin[NP][V], mun[NM][V], hn[NP][V];
-        row_update<R, NP, NM, ANISO, OBST, V, GEN>(c0, n0, k0, Cs, c, phin, mun, hn, tt, x);
+        row_update<R, NP, NM, ANISO, OBST, V, GEN>(c0, n0, k0, Cs, q, phin, mun, hn, tt);
         if constexpr (GEN) {
             htt[1] = htt[0];
             htt[0] = tt;
@@ -160,12 +175,12 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
             ddx(hp[0], tq);
 #pragma unroll
             for (int kk = 0; kk < NM; ++kk) jylo[kk] = R(0);
-            at_face<R, NP, NM, GEN>(hp[1], hp[0], ta, tq, nq[1], nq[0], hu[1], hu[0], ac, jylo, x, htt[1], htt[0]);
+            at_face<R, NP, NM, GEN>(hp[1], hp[0], ta, tq, nq[1], nq[0], hu[1], hu[0], as.a(), jylo, q.x(), htt[1], htt[0]);
         }
     };
     // the current around row q (rows q-1, q, q+1 of phi^n are hp[2], hp[1],
     // hp[0]) and the corrected row q written
-    auto correct = [&](int q) {
+    auto correct = [&](int row) {
         R ty[NP], tyl[NP], pl[NP], ql[NP], ul[NM], txh[NP];
 #pragma unroll
         for (int a = 0; a < NP; ++a) {
@@ -177,10 +192,10 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
 #pragma unroll
         for (int kk = 0; kk < NM; ++kk) ul[kk] = lane_prev(hu[1][kk]);
         R jxl[NM] = {};
-        at_face<R, NP, NM, GEN>(pl, hp[1], tyl, ty, ql, nq[1], ul, hu[1], ac, jxl, x, htt[1], htt[1]);
+        at_face<R, NP, NM, GEN>(pl, hp[1], tyl, ty, ql, nq[1], ul, hu[1], as.a(), jxl, q.x(), htt[1], htt[1]);
         ddx(hp[0], txh);
         R jyhi[NM] = {};
-        at_face<R, NP, NM, GEN>(hp[1], hp[0], tq, txh, nq[1], nq[0], hu[1], hu[0], ac, jyhi, x, htt[1], htt[0]);
+        at_face<R, NP, NM, GEN>(hp[1], hp[0], tq, txh, nq[1], nq[0], hu[1], hu[0], as.a(), jyhi, q.x(), htt[1], htt[0]);
 #pragma unroll
         for (int a = 0; a < NP; ++a) tq[a] = txh[a];
         R hb[NP];
@@ -191,7 +206,8 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
             if constexpr (NP == 3) cross = nq[1][(b + 1) % 3] * nq[1][(b + 2) % 3];
             hb[b] = R(3) * f * f - R(2) * f * f * f + R(2) * f * cross;
         }
-        const int64_t o = (int64_t)q * nx + cs;
+        const int64_t o = (int64_t)row * nx + cs;
+        const AtCoef<R>& ac = as.a();
         if (writes) {
 #pragma unroll
             for (int a = 0; a < NP; ++a) out[a * fs + o] = nq[1][a];
@@ -205,7 +221,7 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
                 mn[kk] = nm[1][kk];
                 jylo[kk] = jyhi[kk];
             }
-            at_correct_gen<R, NP, NM>(hb, dv, ac, *x, mn);
+            at_correct_gen<R, NP, NM>(hb, dv, ac, *q.x(), mn);
             if (writes) {
 #pragma unroll
                 for (int kk = 0; kk < NM; ++kk) out[(NP + kk) * fs + o] = mn[kk];
@@ -263,6 +279,21 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
     }
 }
 
+// The folded kernels' arguments as they lie in memory (x: the general kernel's only).
+template <typename R>
+struct StripAtArgs {
+    const R* in;
+    R* out;
+    Geom g;
+    Coef<R> c;
+    AtCoef<R> ac;
+    const int64_t* stepctr;
+    int kstep;
+    double tb0, tdn, tslope;
+    int seg, ntx, nseg;
+    CoefX<R> x;
+};
+
 template <typename R, int NP, int NM, bool ANISO, bool OBST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MP_WAVES_PER_EU)))
 k_step2d_at(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c, AtCoef<R> ac,
@@ -275,12 +306,15 @@ k_step2d_at(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c, At
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
+    const KernArg<StripAtArgs<R>> ka = (KernArg<StripAtArgs<R>>)__builtin_amdgcn_kernarg_segment_ptr();
+    const CoefSrc<R, true> q{&ka->c, nullptr};
+    const AtSrc<R, true> as{&ka->ac};
     bool fixL, fixR;
     x2_column<1>(g, x2_first_col<1>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)
-        strip2d_at<R, NP, NM, ANISO, OBST, true>(in, out, g, c, ac, tbase, tslope, tx, m0, min(m0 + seg, g.ny));
+        strip2d_at<R, NP, NM, ANISO, OBST, true>(in, out, g, q, as, tbase, tslope, tx, m0, min(m0 + seg, g.ny));
     else
-        strip2d_at<R, NP, NM, ANISO, OBST, false>(in, out, g, c, ac, tbase, tslope, tx, m0, min(m0 + seg, g.ny));
+        strip2d_at<R, NP, NM, ANISO, OBST, false>(in, out, g, q, as, tbase, tslope, tx, m0, min(m0 + seg, g.ny));
 }
 
 // The extended model's general form: the same strip with the GEN arithmetic
@@ -297,14 +331,15 @@ k_step2d_at_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
+    const KernArg<StripAtArgs<R>> ka = (KernArg<StripAtArgs<R>>)__builtin_amdgcn_kernarg_segment_ptr();
+    const CoefSrc<R, true> q{&ka->c, &ka->x};
+    const AtSrc<R, true> as{&ka->ac};
     bool fixL, fixR;
     x2_column<1>(g, x2_first_col<1>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)
-        strip2d_at<R, NP, NM, ANISO, OBST, true, true>(in, out, g, c, ac, tbase, tslope, tx, m0,
-                                                        min(m0 + seg, g.ny), &x);
+        strip2d_at<R, NP, NM, ANISO, OBST, true, true>(in, out, g, q, as, tbase, tslope, tx, m0, min(m0 + seg, g.ny));
     else
-        strip2d_at<R, NP, NM, ANISO, OBST, false, true>(in, out, g, c, ac, tbase, tslope, tx, m0,
-                                                         min(m0 + seg, g.ny), &x);
+        strip2d_at<R, NP, NM, ANISO, OBST, false, true>(in, out, g, q, as, tbase, tslope, tx, m0, min(m0 + seg, g.ny));
 }
 
 // GEN: the general kernel with the extended model's terms x (null otherwise).

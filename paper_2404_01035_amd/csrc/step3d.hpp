@@ -234,7 +234,7 @@ __device__ __forceinline__ void step3d_iso(const R* __restrict__ in, R* __restri
             }
         }
         R phin[NP], mun[NM], h1[NP];
-        cell_update_any<R, NP, NM, OBST, GEN>(C.phi, C.mu, C.h, Gs, Js, Cs, tt, c, x, phin, mun, h1);
+        cell_update_any<R, NP, NM, OBST, GEN>(C.phi, C.mu, C.h, Gs, Js, Cs, tt, CoefSrc<R, false>{c, x}, phin, mun, h1);
         if (valid) store3d<R, NP, NM, GEN, DIAG, NT>(out, g, o0 + (int64_t)m * sz, phin, mun, gy, da, dc);
         __syncthreads();
     };
@@ -410,7 +410,7 @@ __device__ __forceinline__ void step3d_aniso(const R* __restrict__ in, R* __rest
         interp_h<R, NP>(phi, h0);
         R phin[NP], mun[NM];
         R h1[NP];
-        cell_update_any<R, NP, NM, OBST, GEN>(phi, mu, h0, Gs, Js, Cs, tt, c, x, phin, mun, h1);
+        cell_update_any<R, NP, NM, OBST, GEN>(phi, mu, h0, Gs, Js, Cs, tt, CoefSrc<R, false>{c, x}, phin, mun, h1);
         if (valid) store3d<R, NP, NM, GEN, DIAG, NT>(out, g, o0 + (int64_t)m * sz, phin, mun, gy, da, dc);
 
         if (m + 2 <= t.m1) stage(m + 2, uc);

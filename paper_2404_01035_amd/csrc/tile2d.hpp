@@ -119,7 +119,7 @@ __device__ __forceinline__ void tile2d_block(const R* __restrict__ in, R* __rest
             const R tt = (R)((tb0 + tdn * (n + (double)(s - 1))) + tslope * (double)cy);
             psi_const_any<R, NP, GEN>(tt, c, x, Cs);
             R pn[NP], un[NM], h1[NP];
-            cell_update_any<R, NP, NM, OBST, GEN>(phi, mu, h, Gs, Js, Cs, tt, c, x, pn, un, h1);
+            cell_update_any<R, NP, NM, OBST, GEN>(phi, mu, h, Gs, Js, Cs, tt, CoefSrc<R, false>{c, x}, pn, un, h1);
 #pragma unroll
             for (int a = 0; a < NP; ++a) {
                 phi[a] = pn[a];
