@@ -59,17 +59,11 @@ CSRC = os.path.join(ROOT, "paper_2404_01035_amd", "csrc")
 # it was taken on (LEG_SOURCES); otherwise the leg reports traffic null.
 TRAFFIC = {
     # profiles/k_step2d_eutectic_4096_f64_f32.md
-    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "272149d0931cce8d",
-               "bytes": (2.0 * 369660.8 + 667176.8) * 1024},
-    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "cac3a9608d29c2a3",
-               "bytes": (2.0 * 190450.6 + 337887.8) * 1024},
     # profiles/k_step2d_x2_gen_eutectic_4096_f64_f32.md
     # profiles/k_step2d_at_eutectic_4096_f64_f32.md
     # profiles/k_antitrap2d_eutectic_4096_f64_f32.md
     # profiles/k_antitrap3d_dendrite_512_f32.md
     # profiles/k_batch2d_ensemble_256_f32.md
-    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "fefb85abb432b4c9",
-           "bytes": (2.0 * 706252.1 + 1235989.5) * 1024},
 }
 METRIC = "cell-updates/s of fused phi+mu step (FP64 vs FP32), % HBM peak, adjoint/fwd cost"
 ALL_LEGS = ("c2", "c3", "c4", "c5", "at", "ext", "kks")
@@ -210,14 +204,11 @@ def alu_roofline(flops_per_step, ms_step, precision, traffic=None):
 # peaks above: 16 FP64 or 32 FP32 lanes per SIMD per cycle).
 VALU = {
     # profiles/k_step2d_eutectic_4096_f64_f32.md
-    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "272149d0931cce8d", "insts": 153843513.0},
-    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "cac3a9608d29c2a3", "insts": 138091296.0},
     # profiles/k_step2d_x2_gen_eutectic_4096_f64_f32.md
     # profiles/k_step2d_at_eutectic_4096_f64_f32.md
     # profiles/k_antitrap2d_eutectic_4096_f64_f32.md
     # profiles/k_antitrap3d_dendrite_512_f32.md
     # profiles/k_batch2d_ensemble_256_f32.md
-    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "fefb85abb432b4c9", "insts": 468028690.0},
 }
 VALU_CYCLES = {"f64": 4, "f32": 2}
 SIMDS = 1024         # 256 CUs x 4 SIMDs

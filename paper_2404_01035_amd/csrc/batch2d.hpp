@@ -29,7 +29,7 @@ __device__ __forceinline__ void run_strip(const R* src, R* dst, const InstDesc<R
     if constexpr (FUSE == 2)
         strip2d_x2<R, NP, NM, ANISO, OBST, V, true>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, tx, m0, m1);
     else
-        strip2d<R, NP, NM, ANISO, OBST, V, MP_STRIP_DEPTH, BATCH_W>(src, dst, d.g, q, tb0, d.tslope, tx, m0, m1);
+        strip2d<R, NP, NM, ANISO, OBST, V, BATCH_W>(src, dst, d.g, q, tb0, d.tslope, tx, m0, m1);
 }
 
 // Cells per lane of a batched item: 1, or up to VMAX = 2 where nx is even.

@@ -23,7 +23,7 @@ __device__ __forceinline__ void run_strip_gen(const R* src, R* dst, const InstDe
             strip2d_x2<R, NP, NM, ANISO, OBST, 1, true, false, true>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, t,
                                                                     m0, m1);
         else
-            strip2d<R, NP, NM, ANISO, OBST, 1, MP_STRIP_DEPTH, BATCH_W, true>(src, dst, d.g, q, tb0, d.tslope, t, m0,
+            strip2d<R, NP, NM, ANISO, OBST, 1, BATCH_W, true>(src, dst, d.g, q, tb0, d.tslope, t, m0,
                                                                              m1);
     }
 }

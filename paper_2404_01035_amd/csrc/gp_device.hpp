@@ -44,6 +44,52 @@ __device__ __forceinline__ int wrap(int i, int n) {
 
 __device__ __forceinline__ int pair_index(int i, int j) { return i + j - 1; }  // (0,1)->0 (0,2)->1 (1,2)->2
 
+// Marching kernels and the order of their memory operations.  Loads and stores
+// share one counter, and a wave without a cell to write jumps over its stores,
+// so the compiler's wait for a load is a wait for every store before it too.
+// A march therefore issues its loads, computes, waits once (kWaitVm0), takes the
+// landed values over and stores only then: loads and stores alike have a pass of
+// the march to complete in.  Two things keep the compiler from undoing that:
+// moved() copies a landed value out of the registers the next loads go to (left
+// to the compiler that copy is made where the loop starts over, right behind
+// those loads, and waits for them); pin() computes a value before the wait that
+// follows (its arithmetic would otherwise move behind the wait, to the store).
+// A wait at a march's end for its first loads keeps theirs out of the loop's.
+// The row records that this keeps out of each other's way cost fewer registers
+// as well.  Measured, us before and after: 4096^2 eutectic, five steps, FP64
+// 1598 -> 1552 and FP32 930 -> 900; 2048 x 1536 FP64 with slopes, five steps,
+// 438 -> 412; 96 x 80 x 70 FP64, five steps, 136 -> 120 (168 -> 152 VGPRs).
+constexpr unsigned kWaitVm0 = 0x0F70;  // s_waitcnt vmcnt(0), the other counters untouched
+
+__device__ __forceinline__ float moved(float a) {
+    float b;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(b) : "v"(a));
+    return b;
+}
+__device__ __forceinline__ double moved(double a) {
+    double b;
+    asm volatile("v_mov_b64 %0, %1" : "=v"(b) : "v"(a));
+    return b;
+}
+template <typename T, int N>
+__device__ __forceinline__ void moved(const T (&a)[N], T (&b)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if constexpr (std::is_array_v<T>)
+            moved(a[i], b[i]);
+        else
+            b[i] = moved(a[i]);
+}
+template <typename T, int N>
+__device__ __forceinline__ void pin(T (&a)[N]) {
+#pragma unroll
+    for (int i = 0; i < N; ++i)
+        if constexpr (std::is_array_v<T>)
+            pin(a[i]);
+        else
+            asm volatile("" : "+v"(a[i]));
+}
+
 // 1/sqrt(x), x > 0 and normal: hardware estimate (about 1 ulp in FP32), two
 // Newton steps in FP64.
 __device__ __forceinline__ float rsqrt_ok(float x) { return __builtin_amdgcn_rsqf(x); }

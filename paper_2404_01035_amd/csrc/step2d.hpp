@@ -283,10 +283,6 @@ __device__ __forceinline__ void mirror_fix(R (&v)[NF][V], bool fixL, bool fixR) 
     }
 }
 
-#ifndef MP_STRIP_DEPTH
-#define MP_STRIP_DEPTH 2
-#endif
-
 // Diagnostics of one stored row record (V cells of a lane), in FP64; TDEP:
 // B^a depends on T (the extended model).
 template <typename R, int NP, int NM, int V, bool TDEP>
@@ -303,13 +299,11 @@ __device__ __forceinline__ void diag_row(const R (&phin)[NP][V], const R (&mun)[
     }
 }
 
-constexpr unsigned kWaitVm0 = 0x0F70;  // s_waitcnt vmcnt(0), expcnt/lgkmcnt untouched
-
 // One wave's strip of one step: columns tx*W*V .. (tx+1)*W*V - 1 (lanes
 // 1..W, W <= 62), rows [m0, m1).  Called with wave-uniform arguments by the
 // single-grid and the batched kernel.  Requires nx % V == 0.
-template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, int DEPTH = MP_STRIP_DEPTH,
-          int W = W2D_LANES_OUT, bool GEN = false, bool DIAG = false, bool KA = false>
+template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, int W = W2D_LANES_OUT,
+          bool GEN = false, bool DIAG = false, bool KA = false>
 __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
                                         const CoefSrc<R, KA>& q, double tbase, double tslope, int tx,
                                         int m0, int m1,
@@ -346,12 +340,14 @@ __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict_
         make_row<R, NP, NM, ANISO, V, false, GEN>(r.v, P, q);
     };
     Carry2d<R, NP, NM, V, ANISO> k;
-    auto row = [&](int m, const RowT& cur, const RowT& nxt) {
-        R Cs[NP];
+    R phin[NP][V], mun[NM][V];  // the row last computed
+    auto row = [&](const RowT& cur, const RowT& nxt, int m) {
+        R Cs[NP], hn[NP][V];
         const R tt = (R)(tbase + tslope * (double)m);
         psi_const_any<R, NP, GEN>(tt, q.c(), q.x(), Cs);
-        R phin[NP][V], mun[NM][V], hn[NP][V];
         row_update<R, NP, NM, ANISO, OBST, V, GEN>(cur, nxt, k, Cs, q, phin, mun, hn, tt);
+    };
+    auto put = [&](int m) {
         if (writes) {
             const int64_t o = (int64_t)m * nx + cs;
 #pragma unroll
@@ -362,13 +358,17 @@ __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict_
         }
     };
 
-    // Prologue: rows m0-1, m0 and m0+1 processed.
+    // Prologue: rows m0-1, m0 and m0+1 processed, the next two in flight.
     RowT cA, cB;
+    RawT X, Y;
     {
         RawT r0, r1, r2;
         load(m0 - 1, r0);
         load(m0, r1);
         load(m0 + 1, r2);
+        load(min(m0 + 2, m1), X);
+        load(min(m0 + 3, m1), Y);
+        pin(r2.v);  // landed before the loop, whose waits then count only its own loads
         RowT prv;
         process(r0, prv);
         process(r1, cA);
@@ -376,52 +376,31 @@ __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict_
         process(r2, cB);
     }
 
-    // Loads and stores share one counter and may complete out of order with
-    // respect to each other, so the only wait that covers a load issued before
-    // a store is a wait for everything.  The loop therefore waits once per
-    // DEPTH rows and issues the loads of the next DEPTH rows right after that
-    // wait, giving every load DEPTH rows of arithmetic to land in; a raw row
-    // is turned into a cell record just before the row that needs it.
+    // Loads and stores share one counter, and a wave without a lane that writes
+    // jumps over the stores, so a wait for loads is a wait for every store after
+    // them too.  The march therefore waits once per two rows, stores the first
+    // row behind the wait and issues the loads of the two rows after next behind
+    // that: a load has two rows of arithmetic to land in, a store at least one.
     int m = m0;
-    if constexpr (DEPTH == 1) {
-        RawT ld;
-        if (m0 + 2 <= m1) load(m0 + 2, ld);
-        while (true) {
-            row(m, cA, cB);
-            if (++m >= m1) break;
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            process(ld, cA);
-            if (m + 2 <= m1) load(m + 2, ld);
-            row(m, cB, cA);
-            if (++m >= m1) break;
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            process(ld, cB);
-            if (m + 2 <= m1) load(m + 2, ld);
-        }
-    } else {
-        RawT X1, X2, Y1, Y2;
-        if (m0 + 2 <= m1) load(m0 + 2, X1);
-        if (m0 + 3 <= m1) load(m0 + 3, X2);
-        while (true) {
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            if (m + 4 <= m1) load(m + 4, Y1);
-            if (m + 5 <= m1) load(m + 5, Y2);
-            row(m, cA, cB);
-            if (++m >= m1) break;
-            process(X1, cA);
-            row(m, cB, cA);
-            if (++m >= m1) break;
-            process(X2, cB);
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            if (m + 4 <= m1) load(m + 4, X1);
-            if (m + 5 <= m1) load(m + 5, X2);
-            row(m, cA, cB);
-            if (++m >= m1) break;
-            process(Y1, cA);
-            row(m, cB, cA);
-            if (++m >= m1) break;
-            process(Y2, cB);
-        }
+    for (; m + 1 < m1; m += 2) {
+        row(cA, cB, m);
+        pin(phin);
+        pin(mun);
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        RawT x, y;
+        moved(X.v, x.v);
+        moved(Y.v, y.v);
+        put(m);
+        load(min(m + 4, m1), X);
+        load(min(m + 5, m1), Y);
+        process(x, cA);
+        row(cB, cA, m + 1);
+        put(m + 1);
+        process(y, cB);
+    }
+    if (m < m1) {
+        row(cA, cB, m);
+        put(m);
     }
 }
 
@@ -561,8 +540,16 @@ __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restri
             }
         }
         c0 = n0;
-        __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        process(ld, n0);
+    };
+    auto take = [&](RawT& r, RowT& P) {
+        RawT t;
+        moved(r.v, t.v);
+        process(t, P);
+    };
+    // The state row after the window, in flight since the last call, joins it,
+    // and the next one (two on from step-1 row r) is issued.
+    auto next_row = [&](int r) {
+        take(ld, n0);
         load(r + 3 * dir, ld);
     };
 
@@ -571,19 +558,25 @@ __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restri
     {
         RowT outer;
         step1(r_first, outer);
+        next_row(r_first);
         if (first_edge) {
             c1 = outer;
         } else {
             step1(r_first + dir, c1);
+            next_row(r_first + dir);
         }
         carry_init<R, NP, NM, ANISO, V, GEN, DOWN>(outer, c1, k1, src);
     }
+    // Output row q (from step-1 rows c1 and n1), stored by put.
+    R phin[NP][V], mun[NM][V];
     auto step2 = [&](int q) {
-        R Cs[NP];
+        R Cs[NP], hn[NP][V];
         const R tt = (R)(tbase1 + tslope * (double)q);
         psi_const_any<R, NP, GEN>(tt, src.c(), src.x(), Cs);
-        R phin[NP][V], mun[NM][V], hn[NP][V];
         row_update<R, NP, NM, ANISO, OBST, V, GEN, DOWN>(c1, n1, k1, Cs, src, phin, mun, hn, tt);
+        c1 = n1;
+    };
+    auto put = [&](int q) {
         if (writes) {
             const int64_t o = (int64_t)q * nx + cs;
 #pragma unroll
@@ -592,31 +585,33 @@ __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restri
             for (int kk = 0; kk < NM; ++kk) vstore<R, V>(out + (NP + kk) * fs + o, mun[kk]);
             if constexpr (DIAG) diag_row<R, NP, NM, V, GEN>(phin, mun, dc->tt0 + dc->tslope * (double)q, *dc, *da);
         }
-        c1 = n1;
+    };
+    // As in strip2d, a row is stored behind the wait for the row in flight and
+    // before the next loads: loads and stores alike have a pass of the loop, two
+    // rows of arithmetic, to complete in.
+    auto pass = [&](int r, int q) {
+        step1(r, n1);
+        step2(q);
+        pin(phin);
+        pin(mun);
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        take(ld, n0);
+        put(q);
+        load(r + 3 * dir, ld);
     };
     if constexpr (DOWN) {
-        for (int q = m1 - 1; q > m0; --q) {
-            step1(q - 1, n1);
-            step2(q);
-        }
-        // last row: above a no-flux bottom edge step-1 row -1 is a copy of row 0
-        if (top)
-            n1 = c1;
-        else
-            step1(m0 - 1, n1);
-        step2(m0);
+        for (int q = m1 - 1; q > m0; --q) pass(q - 1, q);
     } else {
-        for (int q = m0; q < m1 - 1; ++q) {
-            step1(q + 1, n1);
-            step2(q);
-        }
-        // last row: below a no-flux top edge step-1 row ny is a copy of row ny-1
-        if (bot)
-            n1 = c1;
-        else
-            step1(m1, n1);
-        step2(m1 - 1);
+        for (int q = m0; q < m1 - 1; ++q) pass(q + 1, q);
     }
+    // last row: beyond a no-flux edge the next step-1 row is a copy of this one
+    const int last = DOWN ? m0 : m1 - 1;
+    if (DOWN ? top : bot)
+        n1 = c1;
+    else
+        step1(last + dir, n1);
+    step2(last);
+    put(last);
 }
 
 #ifndef MP_WAVES_PER_EU
@@ -720,7 +715,7 @@ k_step2d_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
-    strip2d<R, NP, NM, ANISO, OBST, 1, MP_STRIP_DEPTH, W2D_LANES_OUT, true>(in, out, g, strip_gen_coef<R>(), tbase,
+    strip2d<R, NP, NM, ANISO, OBST, 1, W2D_LANES_OUT, true>(in, out, g, strip_gen_coef<R>(), tbase,
                                                                           tslope, tx, m0, min(m0 + seg, g.ny));
 }
 
@@ -781,7 +776,7 @@ k_step2d_diag(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
     __shared__ double dls[DS::WORDS];
     DS A;
     A.init(dls, threadIdx.x);
-    strip2d<R, NP, NM, ANISO, OBST, V, MP_STRIP_DEPTH, W2D_LANES_OUT, GEN, true>(
+    strip2d<R, NP, NM, ANISO, OBST, V, W2D_LANES_OUT, GEN, true>(
         in, out, g, CoefSrc<R, false>{c, GEN ? &x : nullptr}, tbase, tslope, tx, m0, min(m0 + seg, g.ny), &A, &d.dc);
     diag_finish(A, d, wid);
 }

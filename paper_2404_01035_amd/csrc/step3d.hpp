@@ -126,9 +126,9 @@ __device__ __forceinline__ void step3d_iso(const R* __restrict__ in, R* __restri
     };
     auto own = [&](Cell& C) {
 #pragma unroll
-        for (int a = 0; a < NP; ++a) C.phi[a] = reg[0][a];
+        for (int a = 0; a < NP; ++a) C.phi[a] = moved(reg[0][a]);
 #pragma unroll
-        for (int k = 0; k < NM; ++k) C.mu[k] = reg[0][NP + k];
+        for (int k = 0; k < NM; ++k) C.mu[k] = moved(reg[0][NP + k]);
         interp_h<R, NP>(C.phi, C.h);
         mobility_any<R, NP, NM, GEN>(C.h, c, x, C.Mt);
     };
@@ -192,11 +192,15 @@ __device__ __forceinline__ void step3d_iso(const R* __restrict__ in, R* __restri
         R Ud[NP];
         face_core<R, NP, NM, false, 0, GEN>(B.phi, A.phi, tau, B.Mt, A.Mt, B.mu, A.mu, c, Ud, Wlo, Jlo);
     }
+    own(B);
     __syncthreads();
 
-    // plane m with its own cells in C; leaves plane m+1's in N
-    auto plane = [&](int m, const Cell& C, Cell& N) {
-        own(N);
+    // Plane m with its own cells in C and plane m+1's in N; leaves plane m+2's
+    // in C.  A wait for loads waits for the stores before them as well (they are
+    // jumped over in a wave outside the grid, so no count of them can be left
+    // out): the plane's loads are issued at its start and waited for before its
+    // stores, so that either has a plane's arithmetic to complete in.
+    auto plane = [&](int m, Cell& C, Cell& N) {
         if (m + 1 < t.m1) stage(m + 1, N);
         if (m + 2 <= t.m1) fetch(m + 2);
         const int sl = m & 1;
@@ -235,6 +239,10 @@ __device__ __forceinline__ void step3d_iso(const R* __restrict__ in, R* __restri
         }
         R phin[NP], mun[NM], h1[NP];
         cell_update_any<R, NP, NM, OBST, GEN>(C.phi, C.mu, C.h, Gs, Js, Cs, tt, CoefSrc<R, false>{c, x}, phin, mun, h1);
+        pin(phin);
+        pin(mun);
+        __builtin_amdgcn_s_waitcnt(kWaitVm0);
+        own(C);
         if (valid) store3d<R, NP, NM, GEN, DIAG, NT>(out, g, o0 + (int64_t)m * sz, phin, mun, gy, da, dc);
         __syncthreads();
     };
@@ -411,9 +419,11 @@ __device__ __forceinline__ void step3d_aniso(const R* __restrict__ in, R* __rest
         R phin[NP], mun[NM];
         R h1[NP];
         cell_update_any<R, NP, NM, OBST, GEN>(phi, mu, h0, Gs, Js, Cs, tt, CoefSrc<R, false>{c, x}, phin, mun, h1);
-        if (valid) store3d<R, NP, NM, GEN, DIAG, NT>(out, g, o0 + (int64_t)m * sz, phin, mun, gy, da, dc);
-
+        // staged before the stores: the wait for the loads would wait for them as well
+        pin(phin);
+        pin(mun);
         if (m + 2 <= t.m1) stage(m + 2, uc);
+        if (valid) store3d<R, NP, NM, GEN, DIAG, NT>(out, g, o0 + (int64_t)m * sz, phin, mun, gy, da, dc);
         const int u = ua;
         ua = ub;
         ub = uc;
