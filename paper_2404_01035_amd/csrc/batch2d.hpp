@@ -21,14 +21,28 @@ constexpr int BATCH_WPB = BATCH_WPB_HOST;  // waves per block
 
 constexpr int BATCH_W = W2X_LANES_OUT;  // written lanes per batched strip
 
+// Whether a strip holds a mirror ghost column.  Only there does the first of two
+// steps make mirror copies and their h (10 lane moves and selects of 640
+// instructions of two rows at N = K = 3).
+// Measured: 64 instances of 64 x 1024 FP32, periodic, 20 steps: 2328 -> 2184 us.
+template <int V>
+__device__ __forceinline__ bool batch_xedge(const Geom& g, int tx) {
+    bool fixL, fixR;
+    x2_column<V>(g, x2_first_col<V>(tx, threadIdx.x & 63), fixL, fixR);
+    return __ballot(fixL || fixR) != 0;
+}
+
 // One item with V cells per lane and FUSE (1 or 2) steps.
 template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, int FUSE>
 __device__ __forceinline__ void run_strip(const R* src, R* dst, const InstDesc<R>& d, double tb0,
                                           double tb1, int tx, int m0, int m1) {
     const CoefSrc<R, false> q{d.c, nullptr};
-    if constexpr (FUSE == 2)
-        strip2d_x2<R, NP, NM, ANISO, OBST, V, true>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, tx, m0, m1);
-    else
+    if constexpr (FUSE == 2) {
+        if (batch_xedge<V>(d.g, tx))
+            strip2d_x2<R, NP, NM, ANISO, OBST, V, true>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, tx, m0, m1);
+        else
+            strip2d_x2<R, NP, NM, ANISO, OBST, V, false>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, tx, m0, m1);
+    } else
         strip2d<R, NP, NM, ANISO, OBST, V, BATCH_W>(src, dst, d.g, q, tb0, d.tslope, tx, m0, m1);
 }
 

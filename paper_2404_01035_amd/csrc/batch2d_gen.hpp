@@ -19,12 +19,16 @@ __device__ __forceinline__ void run_strip_gen(const R* src, R* dst, const InstDe
         const int t = tx * d.vec + sub;
         if (t * BATCH_W >= d.g.nx) break;  // past the instance's last column
         const CoefSrc<R, false> q{d.c, &x};
-        if constexpr (FUSE == 2)
-            strip2d_x2<R, NP, NM, ANISO, OBST, 1, true, false, true>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, t,
-                                                                    m0, m1);
-        else
-            strip2d<R, NP, NM, ANISO, OBST, 1, BATCH_W, true>(src, dst, d.g, q, tb0, d.tslope, t, m0,
-                                                                             m1);
+        if constexpr (FUSE == 2) {
+            if (batch_xedge<1>(d.g, t))
+                strip2d_x2<R, NP, NM, ANISO, OBST, 1, true, false, true>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope,
+                                                                        t, m0, m1);
+            else
+                strip2d_x2<R, NP, NM, ANISO, OBST, 1, false, false, true>(src, dst, nullptr, d.g, q, tb0, tb1,
+                                                                         d.tslope, t, m0, m1);
+        } else {
+            strip2d<R, NP, NM, ANISO, OBST, 1, BATCH_W, true>(src, dst, d.g, q, tb0, d.tslope, t, m0, m1);
+        }
     }
 }
 
