@@ -2,7 +2,8 @@
 //
 // The work list holds one item per (instance, column strip, row segment),
 // strips W2X_LANES_OUT lanes wide for both the one-step and the two-step
-// variant (so the list does not depend on the steps per launch), as
+// variant (so the list does not depend on the steps per launch), or the one
+// strip of a periodic instance whose row fits a wave exactly (strip_ring), as
 // (instance, local index) pairs; the instance table (InstDesc) carries each
 // instance's grid, sizes, coefficients, state offset and temperature law.
 // The grid is sized to what stays resident; the waves of XCD x walk their
@@ -24,7 +25,8 @@ constexpr int BATCH_W = W2X_LANES_OUT;  // written lanes per batched strip
 // Whether a strip holds a mirror ghost column.  Only there does the first of two
 // steps make mirror copies and their h (10 lane moves and selects of 640
 // instructions of two rows at N = K = 3).
-// Measured: 64 instances of 64 x 1024 FP32, periodic, 20 steps: 2328 -> 2184 us.
+// Measured: 64 periodic instances of 64 to 1024 cells a side, FP32, 20 steps:
+// 2328 -> 2184 us.
 template <int V>
 __device__ __forceinline__ bool batch_xedge(const Geom& g, int tx) {
     bool fixL, fixR;
@@ -37,13 +39,16 @@ template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, int FUSE>
 __device__ __forceinline__ void run_strip(const R* src, R* dst, const InstDesc<R>& d, double tb0,
                                           double tb1, int tx, int m0, int m1) {
     const CoefSrc<R, false> q{d.c, nullptr};
+    const bool ring = strip_ring<V>(d.g);
     if constexpr (FUSE == 2) {
         if (batch_xedge<V>(d.g, tx))
             strip2d_x2<R, NP, NM, ANISO, OBST, V, true>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, tx, m0, m1);
         else
-            strip2d_x2<R, NP, NM, ANISO, OBST, V, false>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, tx, m0, m1);
+            strip2d_x2<R, NP, NM, ANISO, OBST, V, false>(src, dst, nullptr, d.g, q, tb0, tb1, d.tslope, tx, m0, m1,
+                                                         (DiagStrip<NP, NM, false>*)nullptr, nullptr, ring);
     } else
-        strip2d<R, NP, NM, ANISO, OBST, V, BATCH_W>(src, dst, d.g, q, tb0, d.tslope, tx, m0, m1);
+        strip2d<R, NP, NM, ANISO, OBST, V, BATCH_W>(src, dst, d.g, q, tb0, d.tslope, tx, m0, m1,
+                                                    (DiagStrip<NP, NM, false>*)nullptr, nullptr, ring);
 }
 
 // Cells per lane of a batched item: 1, or up to VMAX = 2 where nx is even.

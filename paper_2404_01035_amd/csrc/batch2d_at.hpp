@@ -16,9 +16,11 @@ namespace mp {
 template <typename R, int NP, int NM, bool ANISO, bool OBST, bool GEN>
 __device__ __forceinline__ void run_strip_at(const R* src, R* dst, const InstDesc<R>& d, const AtCoef<R>& ac,
                                              const CoefX<R>* x, double tb0, int tx, int m0, int m1) {
-    for (int sub = 0; sub < d.vec; ++sub) {
+    const bool ring = strip_ring<1>(d.g);
+    // (the only strip of an instance covers it, however many strips of one cell per lane it takes)
+    for (int sub = 0; sub < d.vec || d.ntx == 1; ++sub) {
         const int t = tx * d.vec + sub;
-        if (t * W2X_LANES_OUT >= d.g.nx) break;  // past the instance's last column
+        if (t * W2X_LANES_OUT >= d.g.nx || (ring && t > 0)) break;  // past the instance's last column
         bool fixL, fixR;
         x2_column<1>(d.g, x2_first_col<1>(t, threadIdx.x & 63), fixL, fixR);
         if (__ballot(fixL || fixR) != 0)
@@ -26,7 +28,7 @@ __device__ __forceinline__ void run_strip_at(const R* src, R* dst, const InstDes
                                                           d.tslope, t, m0, m1);
         else
             strip2d_at<R, NP, NM, ANISO, OBST, false, GEN>(src, dst, d.g, CoefSrc<R, false>{d.c, x}, AtSrc<R, false>{ac}, tb0,
-                                                          d.tslope, t, m0, m1);
+                                                          d.tslope, t, m0, m1, ring);
     }
 }
 

@@ -15,9 +15,11 @@ namespace mp {
 template <typename R, int NP, int NM, bool ANISO, bool OBST, int FUSE>
 __device__ __forceinline__ void run_strip_gen(const R* src, R* dst, const InstDesc<R>& d, const CoefX<R>& x,
                                               double tb0, double tb1, int tx, int m0, int m1) {
-    for (int sub = 0; sub < d.vec; ++sub) {
+    const bool ring = strip_ring<1>(d.g);
+    // (the only strip of an instance covers it, however many strips of one cell per lane it takes)
+    for (int sub = 0; sub < d.vec || d.ntx == 1; ++sub) {
         const int t = tx * d.vec + sub;
-        if (t * BATCH_W >= d.g.nx) break;  // past the instance's last column
+        if (t * BATCH_W >= d.g.nx || (ring && t > 0)) break;  // past the instance's last column
         const CoefSrc<R, false> q{d.c, &x};
         if constexpr (FUSE == 2) {
             if (batch_xedge<1>(d.g, t))
@@ -25,9 +27,11 @@ __device__ __forceinline__ void run_strip_gen(const R* src, R* dst, const InstDe
                                                                         t, m0, m1);
             else
                 strip2d_x2<R, NP, NM, ANISO, OBST, 1, false, false, true>(src, dst, nullptr, d.g, q, tb0, tb1,
-                                                                         d.tslope, t, m0, m1);
+                                                                         d.tslope, t, m0, m1,
+                                                                         (DiagStrip<NP, NM, true>*)nullptr, nullptr, ring);
         } else {
-            strip2d<R, NP, NM, ANISO, OBST, 1, BATCH_W, true>(src, dst, d.g, q, tb0, d.tslope, t, m0, m1);
+            strip2d<R, NP, NM, ANISO, OBST, 1, BATCH_W, true>(src, dst, d.g, q, tb0, d.tslope, t, m0, m1,
+                                                              (DiagStrip<NP, NM, true>*)nullptr, nullptr, ring);
         }
     }
 }

@@ -73,6 +73,13 @@ __device__ __forceinline__ void vstore(R* p, const R (&v)[V]) {
 constexpr int W2D_LANES_OUT = W2D_LANES_OUT_HOST;  // written lanes per strip wave
 constexpr int W2X_LANES_OUT = W2X_LANES_OUT_HOST;  // written lanes per two-step strip wave
 
+// A periodic row of exactly 64 V columns fits a wave without halo lanes: the
+// lane moves rotate, so lane 63's right neighbour is lane 0, which holds it.
+template <int V>
+__device__ __forceinline__ bool strip_ring(const Geom& g) {
+    return g.bcx == MP_BC_PERIODIC && g.nx == 64 * V;
+}
+
 // Raw row as loaded: the lane's V cells of every field.
 template <typename R, int NF, int V>
 struct Raw2d {
@@ -301,13 +308,14 @@ __device__ __forceinline__ void diag_row(const R (&phin)[NP][V], const R (&mun)[
 
 // One wave's strip of one step: columns tx*W*V .. (tx+1)*W*V - 1 (lanes
 // 1..W, W <= 62), rows [m0, m1).  Called with wave-uniform arguments by the
-// single-grid and the batched kernel.  Requires nx % V == 0.
+// single-grid and the batched kernel.  Requires nx % V == 0.  ring: the wave
+// holds a whole periodic row (strip_ring), tx = 0.
 template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, int W = W2D_LANES_OUT,
           bool GEN = false, bool DIAG = false, bool KA = false>
 __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
                                         const CoefSrc<R, KA>& q, double tbase, double tslope, int tx,
-                                        int m0, int m1,
-                                        DiagStrip<NP, NM, GEN>* da = nullptr, const DiagCoef* dc = nullptr) {
+                                        int m0, int m1, DiagStrip<NP, NM, GEN>* da = nullptr,
+                                        const DiagCoef* dc = nullptr, bool ring = false) {
     constexpr int NF = NP + NM;
     typedef Raw2d<R, NF, V> RawT;
     typedef Row2d<R, NP, NM, V, ANISO, GEN> RowT;
@@ -317,7 +325,7 @@ __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict_
     const int nx = g.nx;
     const int64_t fs = g.fstride;
     static_assert(W >= 1 && W <= 62, "strip width");
-    const int cs = (tx * W - 1 + lane) * V;  // first column of the lane
+    const int cs = ring ? lane * V : (tx * W - 1 + lane) * V;  // first column of the lane
     // load column: the lane's own, or the aligned vector holding its ghost
     int col = cs;
     bool fixL = false, fixR = false;
@@ -328,7 +336,7 @@ __device__ __forceinline__ void strip2d(const R* __restrict__ in, R* __restrict_
         col = perx ? 0 : nx - V;
         fixR = !perx;
     }
-    const bool writes = lane >= 1 && lane <= W && cs < nx;
+    const bool writes = ring || (lane >= 1 && lane <= W && cs < nx);
 
     auto load = [&](int m, RawT& r) {
         const int64_t o = (int64_t)gmap(m, g.ny, pery) * nx + col;
@@ -451,7 +459,8 @@ template <typename R, int NP, int NM, bool ANISO, bool OBST, int V, bool XEDGE, 
 __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restrict__ out, R* __restrict__ out1,
                                            const Geom& g, const CoefSrc<R, KA>& src, double tbase0, double tbase1,
                                            double tslope, int tx, int m0, int m1,
-                                           DiagStrip<NP, NM, GEN>* da = nullptr, const DiagCoef* dc = nullptr) {
+                                           DiagStrip<NP, NM, GEN>* da = nullptr, const DiagCoef* dc = nullptr,
+                                           bool ring = false) {
     constexpr int NF = NP + NM;
     typedef Raw2d<R, NF, V> RawT;
     typedef Row2d<R, NP, NM, V, ANISO, GEN> RowT;
@@ -459,10 +468,10 @@ __device__ __forceinline__ void strip2d_x2(const R* __restrict__ in, R* __restri
     const bool pery = g.bcy == MP_BC_PERIODIC;
     const int nx = g.nx, ny = g.ny;
     const int64_t fs = g.fstride;
-    const int cs = x2_first_col<V>(tx, lane);
+    const int cs = ring ? lane * V : x2_first_col<V>(tx, lane);
     bool fixL, fixR;
     const int col = x2_column<V>(g, cs, fixL, fixR);
-    const bool writes = lane >= 2 && lane <= W2X_LANES_OUT + 1 && cs < nx;
+    const bool writes = ring || (lane >= 2 && lane <= W2X_LANES_OUT + 1 && cs < nx);
     const bool top = !pery && m0 == 0;   // step-1 row -1 is a copy of row 0
     const bool bot = !pery && m1 == ny;  // step-1 row ny is a copy of row ny-1
     // step-1 rows computed: (top ? 0 : m0 - 1) .. (bot ? ny - 1 : m1), from the

@@ -44,7 +44,7 @@ struct AtSrc<R, true> {
 template <typename R, int NP, int NM, bool ANISO, bool OBST, bool XEDGE, bool GEN = false, bool KA = false>
 __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
                                            const CoefSrc<R, KA>& q, const AtSrc<R, KA>& as, double tbase,
-                                           double tslope, int tx, int m0, int m1) {
+                                           double tslope, int tx, int m0, int m1, bool ring = false) {
     constexpr int V = 1;
     constexpr int NF = NP + NM;
     typedef Raw2d<R, NF, V> RawT;
@@ -53,10 +53,10 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
     const bool pery = g.bcy == MP_BC_PERIODIC;
     const int nx = g.nx, ny = g.ny;
     const int64_t fs = g.fstride;
-    const int cs = x2_first_col<V>(tx, lane);
+    const int cs = ring ? lane * V : x2_first_col<V>(tx, lane);
     bool fixL, fixR;
     const int col = x2_column<V>(g, cs, fixL, fixR);
-    const bool writes = lane >= 2 && lane <= W2X_LANES_OUT + 1 && cs < nx;
+    const bool writes = ring || (lane >= 2 && lane <= W2X_LANES_OUT + 1 && cs < nx);
     const bool top = !pery && m0 == 0;   // row -1 is a copy of row 0: its face carries nothing
     const bool bot = !pery && m1 == ny;  // row ny is a copy of row ny-1
     const int r_first = top ? 0 : m0 - 1;

@@ -73,3 +73,32 @@ def test_batches_with_and_without_mirrored_columns(precision, ext):
             assert np.array_equal(a, w), i
         s.close()
     b.close()
+
+
+@pytest.mark.parametrize("precision", ["f64", "f32"])
+@pytest.mark.parametrize("vec", [1, 2])
+@pytest.mark.parametrize("ext,at", [(False, 0), (True, 0), (False, 1), (True, 1)])
+def test_batches_with_rows_that_fit_a_wave(precision, vec, ext, at):
+    """Periodic rows of exactly 64 cells per lane held, one column either side, and the same width with mirrors."""
+    from paper_2404_01035_amd.solver import BatchSolver, Solver
+
+    insts = [_instance((nx, ny, 1), N, K, precision, bc, ext) for nx, ny, N, K, bc in (
+        (64, 33, 3, 3, (0, 1, 0)), (64, 5, 2, 2, (0, 0, 0)), (64, 9, 2, 2, (1, 0, 0)), (128, 9, 3, 2, (0, 0, 0)),
+        (128, 4, 2, 3, (0, 1, 0)), (62, 9, 2, 2, (0, 0, 0)), (66, 9, 3, 3, (0, 0, 0)), (63, 3, 2, 2, (0, 0, 0)),
+        (130, 3, 2, 2, (0, 0, 0)), (192, 3, 2, 2, (0, 0, 0)))]
+    b = BatchSolver([i[0] for i in insts])
+    b.set_tile(32, vec)
+    for i, (_, phi, mu) in enumerate(insts):
+        b.load(i, phi, mu)
+    b.start(0)
+    b.set_antitrapping(at)
+    b.step(5)
+    for i, (p, phi, mu) in enumerate(insts):
+        s = Solver(p)
+        s.load(phi, mu)
+        s.set_antitrapping(at)
+        s.step(5)
+        for a, w in zip(b.fields(i), s.fields()):
+            assert np.array_equal(a, w), i
+        s.close()
+    b.close()
