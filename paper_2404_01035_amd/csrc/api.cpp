@@ -518,9 +518,18 @@ int strips_of(const mp_state* st, const Inst& I, bool rings = true) {
 // counts scale by the same work per cell as a batch's items.  Measured, us per
 // step with the default segment and with the one picked: 64^2 FP64 11.3 / 2.3,
 // 512 x 256 FP32 10.0 / 3.9, 1024^2 FP64 20.3 / 14.5, 4096^2 unchanged.  The
-// default stays unless the model expects over 4 % from a shorter one.
+// default stays unless the model expects over 4 % from a shorter one.  The 2D
+// families' fits (strip_model) pick within 0-2 % of the best of 1 .. 31 rows on
+// average over eleven grids from 300 x 200 to 4096^2; one pair of fits for all
+// of them was 0.4-8 % off, at worst 30 % (anti-trapping, general, FP32 1024^2:
+// 28.2 us per step, now 24.4).
+//     With `resident` set the latency is paid once per that many waves of a
+// SIMD: the general FP64 kernel holds two (182 registers), so a third wave per
+// SIMD waits for one to end (2048 x 1536: 27 rows, two waves, 41.1 us per step;
+// 18 rows, three, 42.9).
 struct SegModel {
     double halo, alpha, beta;
+    int resident = 1 << 30;
 };
 constexpr double kSegLaunch = 3.5;  // us of a launch that no row pays for
 constexpr int kChipCus = 256;       // of the part the fits were made on
@@ -540,7 +549,7 @@ double seg_cost(const SegModel& m, double weight, int64_t across, int64_t rows, 
     const int64_t waves = across * ((rows + seg - 1) / seg) * wpb;
     const double k = (double)((waves + 4 * kChipCus - 1) / (4 * kChipCus));
     const double len = (double)std::min<int64_t>(seg, rows);
-    return kSegLaunch + weight * (len + m.halo) * (m.alpha + m.beta * k);
+    return kSegLaunch + weight * (len + m.halo) * (m.alpha * std::ceil(k / m.resident) + m.beta * k);
 }
 
 // Shortest expected launch over the segment lengths 1 .. cap.
@@ -561,9 +570,12 @@ int best_seg(const SegModel& m, double weight, int64_t across, int64_t rows, int
 // The 2D strips of `fuse` steps (at: with the current folded in): model and strips per row of segments.
 SegModel strip_model(const mp_state* st, int fuse, bool at) {
     const bool f64 = st->precision == MP_FP64;
-    if (at) return f64 ? SegModel{3.0, 0.7, 0.95} : SegModel{3.0, 0.7, 0.6};
-    const SegModel m = f64 ? SegModel{2.0, 0.2, 0.95} : SegModel{2.0, 0.75, 0.37};
-    return fuse == 1 ? SegModel{m.halo, 0.5 * m.alpha, 0.5 * m.beta} : m;
+    const bool gen = st->inst[0].ext;
+    if (at && gen) return f64 ? SegModel{1.8, 0.9, 0.65} : SegModel{2.05, 0.92, 0.3};
+    if (at) return f64 ? SegModel{1.85, 0.8, 0.86} : SegModel{2.05, 1.06, 0.37};
+    const SegModel m = gen ? (f64 ? SegModel{1.93, 0.86, 0.49, 2} : SegModel{2.2, 0.8, 0.37})
+                           : (f64 ? SegModel{2.3, 0.23, 0.89} : SegModel{2.4, 0.65, 0.41});
+    return fuse == 1 ? SegModel{m.halo, 0.5 * m.alpha, 0.5 * m.beta, m.resident} : m;
 }
 int64_t strip_count(const mp_state* st, int fuse, bool at) {
     const Inst& I = st->inst[0];
