@@ -54,11 +54,12 @@ __device__ __forceinline__ int pair_index(int i, int j) { return i + j - 1; }  /
 // to the compiler that copy is made where the loop starts over, right behind
 // those loads, and waits for them); pin() computes a value before the wait that
 // follows (its arithmetic would otherwise move behind the wait, to the store).
+// (The one-step 2D strip, bound by memory, is not in this order; see there.)
 // A wait at a march's end for its first loads keeps theirs out of the loop's.
 // The row records that this keeps out of each other's way cost fewer registers
-// as well.  Measured, us before and after: 4096^2 eutectic, five steps, FP64
-// 1598 -> 1552 and FP32 930 -> 900; 2048 x 1536 FP64 with slopes, five steps,
-// 438 -> 412; 96 x 80 x 70 FP64, five steps, 136 -> 120 (168 -> 152 VGPRs).
+// as well.  Measured, us before and after: 4096^2 eutectic, ten steps, FP64
+// 1598 -> 1552 and FP32 930 -> 900; 2048 x 1536 FP64 with slopes, ten steps,
+// 438 -> 412; 96 x 80 x 70 FP64, eight steps, 136 -> 120 (168 -> 152 VGPRs).
 constexpr unsigned kWaitVm0 = 0x0F70;  // s_waitcnt vmcnt(0), the other counters untouched
 
 __device__ __forceinline__ float moved(float a) {
@@ -124,7 +125,7 @@ __device__ __forceinline__ void store_cell(R* __restrict__ out, int64_t fs, int6
 // general FP64 kernel, 160 of 1173 of a row with the anti-trapping current.
 // Reading them again costs scalar loads from cached constant memory instead.
 // Measured: general FP64 kernel, eutectic with slopes 2048 x 1536, 457 -> 438
-// us per five steps of the public call.  Not worth it where few are parked: the
+// us per ten steps of the public call.  Not worth it where few are parked: the
 // plain FP64 kernel and FP32 lose nothing to it and gain nothing.
 // The empty asm hides where the pointer came from, which keeps the loads inside
 // the loop and each use's registers to itself.
