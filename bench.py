@@ -55,7 +55,7 @@ CSRC = os.path.join(ROOT, "paper_2404_01035_amd", "csrc")
 # HBM bytes per launch of each leg's step kernel, from rocprofv3 counter runs:
 # FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (KiB), the factors being what the same
 # counters read for a plain device copy of known size.  A figure holds only
-# for the tile and steps per launch it was taken at and for the device sources
+# for the launched tile and steps per launch it was taken at and for the device sources
 # it was taken on (LEG_SOURCES); otherwise the leg reports traffic null.
 TRAFFIC = {
     # profiles/counters_all_legs.md
@@ -67,7 +67,7 @@ TRAFFIC = {
         "bytes": (2.0 * 384631.9 + 655914.3) * 1024},
     "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "2b6d6ff7abfec536",
         "bytes": (2.0 * 224288.2 + 328204.2) * 1024},
-    "c3": {"tile": [512, 64, -1], "fuse": 1, "src": "b01cc51c273929b6",
+    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "643f3659e1eb54bd",
         "bytes": (2.0 * 962720.0 + 1572864.0) * 1024},
     "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "9c091efbc5694c42",
         "bytes": (2.0 * 396150.6 + 669848.1) * 1024},
@@ -225,7 +225,7 @@ VALU = {
     "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "0878b850b4918ae2", "insts": 137889195.0},
     "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "6a7eb1ff425999d4", "insts": 195920541.0},
     "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "2b6d6ff7abfec536", "insts": 169620984.0},
-    "c3": {"tile": [512, 64, -1], "fuse": 1, "src": "b01cc51c273929b6", "insts": 551390957.0},
+    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "643f3659e1eb54bd", "insts": 551390957.0},
     "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "9c091efbc5694c42", "insts": 135827199.0},
     "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "9c091efbc5694c42", "insts": 120842193.0},
     "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "7fc8c2db2799a624", "insts": 65303901.0},
@@ -275,6 +275,15 @@ def with_counter_fracs(rec, ms_launch, precision, traffic=None, valu_insts=None)
     rec["valu_issue_frac"] = None if valu_insts is None else round(
         valu_insts * VALU_CYCLES[precision] / SIMDS / CLOCK_HZ / (ms_launch * 1e-3), 4)
     return rec
+
+
+def launched_tile(st, steps):
+    """[bx, seg, vec] of the launches that ``steps`` steps make (mp_get_tile reports the
+    default, which a launch may shorten); [region^2, 0, vec] by the tile kernel."""
+    from paper_2404_01035_amd import abi
+
+    _, bx, seg, _ = abi.mp_get_launches(st, max(1, steps))
+    return [bx, seg, abi.mp_get_tile(st)[2]]
 
 
 def parse_tile(text):
@@ -421,7 +430,7 @@ def leg_c2(precision, n, steps, warmup, tile, tune, slopes=False, kks=None):
         source = "tuned"
     else:
         source = "default"
-    used = list(abi.mp_get_tile(s.st))
+    used = launched_tile(s.st, steps)
     fuse = abi.mp_get_fusion(s.st)
     ms, regions, settle = measure(s.step, steps, warmup)
     d = s.diagnostics()
@@ -492,7 +501,6 @@ def leg_at(precision, n, steps, warmup):
     separate correction kernel.  The same run without the current (one step per
     launch) is timed first; the difference of the separate path's and the plain
     step's median regions is the correction kernel's time per step."""
-    from paper_2404_01035_amd import abi
     from paper_2404_01035_amd.solver import Solver
     from paper_2404_01035_amd import inputs
 
@@ -506,7 +514,7 @@ def leg_at(precision, n, steps, warmup):
     ms2, regions2, _ = measure(s.step, steps, warmup)
     s.set_antitrapping(1)
     ms1, regions, _ = measure(s.step, steps, warmup)
-    bx, seg, _ = abi.mp_get_tile(s.st)
+    bx, seg, _ = launched_tile(s.st, steps)
     d = s.diagnostics()
     s.close()
     elem = 8 if precision == "f64" else 4
@@ -556,7 +564,7 @@ def leg_c3(n, steps, warmup, tile, tune):
         s.set_tile(*tile)
     elif tune:
         s.autotune(reps=5, force=True)
-    used = list(abi.mp_get_tile(s.st))
+    used = launched_tile(s.st, steps)
     ms, regions, settle = measure(s.step, steps, warmup)
     d = s.diagnostics()
     dt = diag_timing(s, 1)
@@ -602,7 +610,7 @@ def leg_c4(steps, warmup, tile, tune, graph_chunk=50):
         b.set_tile(*tile)
     elif tune:
         b.autotune(reps=5, force=True)
-    used = list(abi.mp_get_tile(b.st))
+    used = launched_tile(b.st, steps)
     fuse = abi.mp_get_fusion(b.st)
     b.set_graph(graph_chunk)
     ms, regions, _ = measure(b.step, steps, warmup)

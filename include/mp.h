@@ -268,16 +268,25 @@ int mp_diagnostics_static(const mp_state* st, const void* state_buf, int64_t ste
  * vec = the most cells one lane holds (1, 2, or 4 in FP32 only; each lane
  * takes the largest power of two <= vec that divides nx; -1 = the widest the
  * precision allows).  A batched state takes bx = 256 and vec in {-1, 1, 2}
- * (-1 acts as 2).  3D: bx = 256 (32 x 8 tiles) or 512 (64 x 8 tiles, where
- * the tile's LDS ring fits in 64 KiB), seg = z planes per block, vec must be
- * 0 or 1.  0 keeps the current value of a
- * field.  Until seg is given here (or by MP_TILE or mp_tune), a launch on a
- * grid too small to fill the GPU with the default's segments takes shorter
- * ones, and a small 2D grid several steps per launch (mp_step) until any of
- * the three is given; mp_get_tile reports the default.  Results do not depend on the tile
- * shape (bitwise). */
+ * (-1 acts as 2).  3D: bx = 256 (32 x 8 tiles) or 512 (64 x 8 tiles, FP32
+ * with N + 2 (K - 1) <= 6), seg = z planes per block, vec must be 0 or 1.
+ * 0 keeps the current value of a field.  Until seg is given here (or by
+ * MP_TILE or mp_tune), a launch on a grid too small to fill the GPU with the
+ * default's segments takes shorter ones, and a small 2D grid several steps per
+ * launch (mp_step) until any of the three is given; mp_get_tile reports the
+ * default, mp_get_launches what is launched.  Results do not depend on the
+ * tile shape (bitwise). */
 int mp_set_tile(mp_state* st, int bx, int seg, int vec);
 int mp_get_tile(const mp_state* st, int* bx, int* seg, int* vec);
+
+/* How mp_step(st, nsteps) would be launched without graphs: ``count`` launches
+ * of the step kernel with ``bx`` threads per block and ``seg`` rows (3D:
+ * planes) per segment -- of the launches of the most steps, where a remainder
+ * takes fewer -- and ``region`` = 0; or, on a small 2D grid at the default
+ * tile, several steps each on regions of ``region`` x ``region`` cells
+ * (bx = region^2, seg = 0).  Any pointer but st may be NULL.  No GPU work.
+ * Errors: MP_E_NULLPTR, MP_E_PARAM (nsteps < 1). */
+int mp_get_launches(const mp_state* st, int64_t nsteps, int64_t* count, int* bx, int* seg, int* region);
 
 /* Autotuning support.  mp_tune_candidates writes up to ``cap`` candidates
  * (bx, seg, vec, steps per launch) valid for this state into

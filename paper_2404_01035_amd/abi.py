@@ -37,7 +37,7 @@ EXPORTS = [
     "mp_diagnostics_batch", "mp_step_ckpt", "mp_adjoint_work_bytes", "mp_adjoint",
     "mp_tune_candidates", "mp_tune", "mp_set_fusion", "mp_get_fusion",
     "mp_set_antitrapping", "mp_get_antitrapping", "mp_diagnostics_static", "mp_front_row", "mp_shift",
-    "mp_step_diag",
+    "mp_step_diag", "mp_get_launches",
 ]
 
 # Layout of the parameter gradient filled by mp_adjoint.
@@ -120,6 +120,9 @@ def lib():
         L.mp_set_tile.argtypes = [vp, C.c_int, C.c_int, C.c_int]
         L.mp_get_tile.restype = C.c_int
         L.mp_get_tile.argtypes = [vp, C.POINTER(C.c_int), C.POINTER(C.c_int), C.POINTER(C.c_int)]
+        L.mp_get_launches.restype = C.c_int
+        L.mp_get_launches.argtypes = [vp, C.c_int64, C.POINTER(C.c_int64), C.POINTER(C.c_int), C.POINTER(C.c_int),
+                                      C.POINTER(C.c_int)]
         L.mp_destroy.restype = None
         L.mp_destroy.argtypes = [vp]
         L.mp_last_error.restype = C.c_char_p
@@ -379,6 +382,13 @@ def mp_get_tile(st):
     bx, seg, vec = C.c_int(), C.c_int(), C.c_int()
     _check(lib().mp_get_tile(st, C.byref(bx), C.byref(seg), C.byref(vec)))
     return bx.value, seg.value, vec.value
+
+
+def mp_get_launches(st, nsteps: int):
+    """(launches, bx, seg, region) of nsteps steps; region > 0: by the tile kernel."""
+    count, bx, seg, region = C.c_int64(), C.c_int(), C.c_int(), C.c_int()
+    _check(lib().mp_get_launches(st, int(nsteps), C.byref(count), C.byref(bx), C.byref(seg), C.byref(region)))
+    return count.value, bx.value, seg.value, region.value
 
 
 def mp_destroy(st):

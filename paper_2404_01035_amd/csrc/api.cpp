@@ -588,22 +588,18 @@ double strip_cost(const mp_state* st, int fuse, int seg) {
                     st->inst[0].grid.n[1], 1, seg);
 }
 
-// Threads per block of a single-grid launch: without a tile set, 3D takes the
-// 256-thread tiles whatever the default (call_3d has both measured).
-int launch_bx(const mp_state* st) { return st->inst[0].grid.dim == 3 && st->tile_auto ? 256 : st->bx; }
-
 // Segment of a single-grid launch of `fuse` steps (at: with the current folded in).
 int launch_seg(const mp_state* st, int fuse, bool at) {
     if (!st->seg_auto) return st->seg;
     const Inst& I = st->inst[0];
     const mp_grid& g = I.grid;
     if (g.dim == 3) {
-        // tiles of 32 x 8 (launch_bx 256) or 64 x 8; a 3D face's anisotropy costs
+        // tiles of 32 x 8 (bx 256) or 64 x 8; a 3D face's anisotropy costs
         // latency, not issue slots (most of it is skipped where |q| is small)
         const bool f64 = st->precision == MP_FP64;
         const SegModel m = I.aniso ? (f64 ? SegModel{3.0, 2.0, 1.2} : SegModel{3.0, 1.7, 0.48})
                                    : (f64 ? SegModel{3.0, 0.55, 0.6} : SegModel{3.0, 0.6, 0.5});
-        const int tx = launch_bx(st) == 512 && !I.ext ? 64 : 32;
+        const int tx = st->bx == 512 && !I.ext ? 64 : 32;
         const double w = cell_weight(I.N, I.K - 1) / cell_weight(3, 2) * (I.ext ? 1.4 : 1.0);
         return best_seg(m, w, ((g.n[0] + tx - 1) / tx) * ((g.n[1] + 7) / 8), g.n[2], tx / 8, st->seg);
     }
@@ -1009,7 +1005,7 @@ int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr
     L.dim = I.grid.dim;
     L.potential = kernel_potential(I.prm.potential);
     L.aniso = I.aniso ? 1 : 0;
-    L.bx = launch_bx(st);
+    L.bx = st->bx;
     L.seg = launch_seg(st, fuse, at_folded(st) && !out1 && !diag);
     L.vec = st->vec;
     L.fuse = fuse;
@@ -1114,7 +1110,7 @@ int build_graph(mp_state* st, int from, hipGraphExec_t* out) {
     return rc;
 }
 
-// 3D tiles of 64 x 8 exist where their LDS ring fits in 64 KiB.
+// 3D tiles of 64 x 8 are accepted for FP32 with N + 2 (K - 1) <= 6 (lds3d_bytes).
 bool d3_tall_ok(const mp_state* st) {
     const Inst& I = st->inst[0];
     const int elem = (int)elem_of(st->precision);
@@ -1144,8 +1140,8 @@ void init_state(mp_state* st) {
     st->seg_auto = st->tile_auto = true;
     st->potential = kernel_potential(st->inst[0].prm.potential);
     if (st->inst[0].grid.dim == 3) {
-        // measured best on 512^3 FP32: tall tiles, long z segments
-        st->bx = d3_tall_ok(st) ? 512 : 256;
+        // measured best on 512^3 FP32: 32 x 8 tiles (call_3d has all shapes), long z segments
+        st->bx = 256;
         st->seg = 64;
     } else if (st->batch) {
         // measured best on the 256-instance ensemble: two steps per launch,
@@ -1710,6 +1706,17 @@ int mp_get_tile(const mp_state* st, int* bx, int* seg, int* vec) {
     if (bx) *bx = st->bx;
     if (seg) *seg = st->seg;
     if (vec) *vec = st->vec;
+    return ok();
+}
+
+int mp_get_launches(const mp_state* st, int64_t nsteps, int64_t* count, int* bx, int* seg, int* region) {
+    if (!st) return fail(MP_E_NULLPTR, "state is NULL");
+    if (nsteps < 1) return fail(MP_E_PARAM, "nsteps must be >= 1");
+    const Schedule S = schedule(st, nsteps);
+    if (count) *count = S.count;
+    if (bx) *bx = S.tw > 0 ? S.tw * S.tw : st->bx;
+    if (seg) *seg = S.tw > 0 ? 0 : (st->batch ? batch_seg(st) : launch_seg(st, launch_fuse(st), at_folded(st)));
+    if (region) *region = S.tw;
     return ok();
 }
 

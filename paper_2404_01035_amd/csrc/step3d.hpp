@@ -582,7 +582,9 @@ int call_3d_by(const StepLaunch& L, const Coef<R>& c, KernelCall& k) {
 
 // bx = threads per block: 256 (32 x 8 tiles: a row is one 128-byte line in
 // FP32, and the halo, 1.33 staged cells per cell, is the smallest for the size)
-// or 512 (64 x 8), accepted where four planes of all its records fit in 64 KiB.
+// or 512 (64 x 8), accepted where four planes of phi, mu and M~ of such a tile
+// fit in 64 KiB: FP32 with N + 2 (K - 1) <= 6 (the kernels keep fewer planes than
+// that; the rule is what mp_set_tile has always taken).
 // FP32 512^3 anisotropic: 897 us with 32 x 8 tiles, 913 with 64 x 4, 904 with
 // 64 x 8; FP64 256^3 with three phases 318 / 336 us (32 x 8, 64 x 4). The
 // diagnostics instances take 64 x 4 and 64 x 8.
