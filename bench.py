@@ -67,7 +67,7 @@ TRAFFIC = {
         "bytes": (2.0 * 384631.9 + 655914.3) * 1024},
     "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "2b6d6ff7abfec536",
         "bytes": (2.0 * 224288.2 + 328204.2) * 1024},
-    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "643f3659e1eb54bd",
+    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "8863990089505028",
         "bytes": (2.0 * 962720.0 + 1572864.0) * 1024},
     "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "9c091efbc5694c42",
         "bytes": (2.0 * 396150.6 + 669848.1) * 1024},
@@ -225,7 +225,7 @@ VALU = {
     "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "0878b850b4918ae2", "insts": 137889195.0},
     "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "6a7eb1ff425999d4", "insts": 195920541.0},
     "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "2b6d6ff7abfec536", "insts": 169620984.0},
-    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "643f3659e1eb54bd", "insts": 551390957.0},
+    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "8863990089505028", "insts": 551390957.0},
     "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "9c091efbc5694c42", "insts": 135827199.0},
     "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "9c091efbc5694c42", "insts": 120842193.0},
     "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "7fc8c2db2799a624", "insts": 65303901.0},

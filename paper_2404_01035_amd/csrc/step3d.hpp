@@ -447,12 +447,18 @@ __device__ __forceinline__ void step3d_block(const R* __restrict__ in, R* __rest
                                                        nty, x, da, dc);
 }
 
-// FP64 at three waves per SIMD: the isotropic kernel of three phases and two mu
-// fields fits them without spills (182 registers otherwise).
-#define MP3_WAVES(R) (sizeof(R) == 8 ? 3 : 2)
+// FP64 at three waves per SIMD where the kernel fits their 168 registers: the
+// isotropic plain ones (three phases and two mu fields take 182 otherwise) and
+// the isotropic general ones of up to four fields without an obstacle.  The
+// others are left to their registers: bound to three waves they spilled up to
+// 91 of them.  Measured, us per step of 256^3, bound / free: three phases and
+// one mu field, anisotropic, 1107 / 655, general with the active-set obstacle
+// 1404 / 629; general isotropic of five fields 784 / 370, of four with the
+// obstacle 292 / 259 and 286 / 275, of four without 249 / 267 and 253 / 254.
+#define MP3_WAVES(R, FITS) (sizeof(R) == 4 ? 2 : (FITS) ? 3 : 1)
 
 template <typename R, int NP, int NM, bool ANISO, bool OBST, int BX, int BY, bool NT>
-__global__ void __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(MP3_WAVES(R))))
+__global__ void __launch_bounds__(BX * BY) __attribute__((amdgpu_waves_per_eu(MP3_WAVES(R, !ANISO))))
 k_step3d(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
          const int64_t* __restrict__ stepctr, int kstep, double tb0, double tdn, double tslope,
          int seg, int ntx, int nty) {
@@ -462,7 +468,7 @@ k_step3d(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
 
 // The extended model's 3D kernel (32 x 8 tiles).
 template <typename R, int NP, int NM, bool ANISO, bool OBST>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MP3_WAVES(R))))
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MP3_WAVES(R, !ANISO && !OBST && NP + NM < 5))))
 k_step3d_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
              const int64_t* __restrict__ stepctr, int kstep, double tb0, double tdn, double tslope,
              int seg, int ntx, int nty, CoefX<R> x) {
