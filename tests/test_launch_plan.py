@@ -1,6 +1,7 @@
 """What mp_step launches (mp_get_launches), host side: no GPU needed."""
 import ctypes as C
 
+import numpy as np
 import pytest
 
 from paper_2404_01035_amd import abi, inputs
@@ -53,3 +54,20 @@ def test_argument_errors(state):
     assert L.mp_get_launches(st, 0, None, None, None, None) == abi.MP_E_PARAM
     n = C.c_int64()
     assert L.mp_get_launches(st, 1, C.byref(n), None, None, None) == abi.MP_OK and n.value == 1
+
+
+def test_3d_segments_where_a_simd_holds_one_wave(state):
+    # FP64, anisotropic, general, five fields: the second block of a CU waits for the
+    # first, so 256^3 keeps the longest segments and 96 x 80 x 70 (30 tiles) takes
+    # segments that make one round of at most 256 blocks
+    p, _, _ = inputs.random_instance(np.random.default_rng(7), 16, 16, 3, 3, nuclei=1)
+    p.delta[:, :] = 0.02 * (1.0 - np.eye(3))
+    p.Bt[:3, :2] = 0.05
+
+    def seg(n):
+        q = p.copy(n=n, dim=3, precision="f64")
+        q.dt = 0.2 * inputs.dt_limit(q)
+        return abi.mp_get_launches(state(q), 1)[2]
+
+    assert seg((256, 256, 256)) == 64
+    assert 30 * -(-70 // seg((96, 80, 70))) <= 256
