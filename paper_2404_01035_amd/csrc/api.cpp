@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -80,6 +81,7 @@ struct mp_state {
     std::vector<mp::KernelCall> gcalls[2];  // argument records of each graph's nodes, kept alive
     std::vector<int> items;  // batch work list (host copy): (instance, local item) pairs
     int nitems;
+    int item_seg;            // rows per item
     mp::BatchCuts cuts;      // first item of each XCD's slice of the list, and the end
     int batch_blocks;
     // adjoint: a second stream (default priority) that recomputes the next
@@ -624,23 +626,117 @@ int at3_seg(const mp_state* st) {
                     g.n[2], 1, 64);
 }
 
-// Segment of a batch's work items (one for all its launches: the instance
-// table holds it).
-int batch_seg(const mp_state* st) {
-    if (!st->seg_auto) return st->seg;
-    // as if every strip were as long as the mean one; the uneven deal and the
-    // mirror copies of every strip blur the model, so a shorter segment has to
-    // promise 10 % (8 instances of 64^2 .. 1024^2: 58.0 us per step at 32 rows,
-    // 33.7 at 8; 64 instances: 121.8 at 32, 123.6 at 16)
-    const SegModel m = st->precision == MP_FP64 ? SegModel{3.0, 0.2, 0.95} : SegModel{3.0, 0.75, 0.37};
-    int64_t strips = 0;
-    double rows = 0.0;
-    for (const Inst& I : st->inst) {
-        strips += strips_of(st, I);
-        rows += (double)strips_of(st, I) * (double)I.grid.n[1];
+// A batch with an instance of the extended model steps every instance with the general kernels.
+bool batch_gen(const mp_state* st) {
+    for (const Inst& I : st->inst)
+        if (I.ext) return true;
+    return false;
+}
+
+// ---- segment of a batch's work items (one for all its launches) ----------------
+// FP32: SegModel on the strips of all instances and their mean rows.  In FP64
+// that picked up to 20 % worse than the default (8 instances of 64 to 1024
+// cells a side: 50 us per step with 32 rows, 60 with the 23 picked): uneven
+// instances go to the XCDs whole (arrange_items), and with few waves per SIMD
+// the one that is dealt the most decides what a launch lasts.  There the deal is
+// played through for each segment, a SIMD lasting about
+//     alpha (rows of its longest wave) + beta (rows of all its waves),
+// rows weighted by their cells' work and counted with the halo rows.  Fitted,
+// like SegModel, to 10-step runs of six ensembles of 4 to 128 instances with 2
+// to 32 rows, plain, anisotropic, general and with the current, one and two
+// steps per launch: the picks take 1.5 % longer than the best of nine lengths
+// on average, SegModel's 18 %.  Measured, us per step with 32 rows / SegModel's
+// pick / this one's: the 8 instances 50 / 60 / 45, 24 of 128 to 400 with the
+// current 99 / 100 / 54.  (In FP32 SegModel's picks are within 4 % of the best
+// on average, and the deal's were up to 14 % slower on 32 of 64 to 700.)
+//     The first shorter segment has to promise 10 %, in FP64 each further one 3 %.
+struct DealModel {
+    double alpha, beta;
+    int waves;  // per SIMD
+};
+constexpr int kBatchSegs[] = {28, 24, 20, 16, 12, 8, 6, 4, 3, 2, 1};
+
+double deal_cost(const mp_state* st, const DealModel& m, int seg, double give_up) {
+    struct Group {  // items of equal cost
+        double cost;
+        int64_t count;
+    };
+    constexpr double halo = 3.0;
+    const double work = (st->aniso ? 2.1 : 1.0) * (batch_gen(st) ? 1.4 : 1.0) / cell_weight(3, 2);
+    std::vector<std::array<Group, 2>> of(st->inst.size());
+    std::vector<std::pair<double, size_t>> order;
+    double total = 0.0;
+    int64_t nitems = 0;
+    for (size_t i = 0; i < st->inst.size(); ++i) {
+        const Inst& I = st->inst[i];
+        const double w = work * vec_of(st, I) * cell_weight(I.N, I.K - 1);
+        const int64_t strips = strips_of(st, I), full = I.grid.n[1] / seg, rest = I.grid.n[1] % seg;
+        of[i] = {Group{w * (seg + halo), strips * full}, Group{w * ((double)rest + halo), rest ? strips : 0}};
+        const double c = of[i][0].cost * (double)of[i][0].count + of[i][1].cost * (double)of[i][1].count;
+        order.push_back({-c, i});
+        total += c;
+        nitems += of[i][0].count + of[i][1].count;
     }
-    return best_seg(m, 1.0, strips, std::max<int64_t>(1, (int64_t)(rows / (double)strips)), 1, st->seg,
-                    0.9);
+    constexpr int simds = 4 * kChipCus / 8;  // of an XCD
+    if (kSegLaunch + m.beta * total / (8 * simds) >= give_up) return give_up;
+    std::sort(order.begin(), order.end());
+    std::vector<Group> slice[8];
+    double load[8] = {0, 0, 0, 0, 0, 0, 0, 0};
+    for (const auto& o : order) {
+        const int x = (int)(std::min_element(load, load + 8) - load);
+        load[x] -= o.first;
+        for (const Group& g : of[o.second])
+            if (g.count) slice[x].push_back(g);
+    }
+    const int64_t need = (nitems + mp::BATCH_WPB_HOST - 1) / mp::BATCH_WPB_HOST;
+    const int64_t wpx = (std::min<int64_t>(need, (int64_t)kChipCus * m.waves) + 7) / 8 * mp::BATCH_WPB_HOST;
+    double longest = 0.0;
+    std::vector<double> wave(wpx);
+    for (std::vector<Group>& v : slice) {
+        std::stable_sort(v.begin(), v.end(), [](const Group& a, const Group& b) { return a.cost > b.cost; });
+        int64_t n = 0, p = 0;
+        for (const Group& g : v) n += g.count;
+        std::fill(wave.begin(), wave.end(), 0.0);
+        for (const Group& g : v)
+            for (int64_t q = 0; q < g.count; ++q, ++p) {
+                const int64_t r0 = p / wpx * wpx, len = std::min(wpx, n - r0);
+                wave[(p / wpx) % 2 ? len - 1 - (p - r0) : p - r0] += g.cost;
+            }
+        for (int s = 0; s < simds; ++s) {
+            double most = 0.0, sum = 0.0;
+            for (int64_t w = s; w < wpx; w += simds) {
+                most = std::max(most, wave[w]);
+                sum += wave[w];
+            }
+            longest = std::max(longest, m.alpha * most + m.beta * sum);
+        }
+    }
+    return kSegLaunch + longest;
+}
+
+int pick_batch_seg(const mp_state* st) {
+    if (!st->seg_auto) return st->seg;
+    if (st->precision == MP_FP32) {
+        int64_t strips = 0;
+        double rows = 0.0;
+        for (const Inst& I : st->inst) {
+            strips += strips_of(st, I);
+            rows += (double)strips_of(st, I) * (double)I.grid.n[1];
+        }
+        return best_seg(SegModel{3.0, 0.75, 0.37}, 1.0, strips,
+                        std::max<int64_t>(1, (int64_t)(rows / (double)strips)), 1, st->seg, 0.9);
+    }
+    const DealModel m{0.5, 0.8, 3};
+    int best = st->seg;
+    double tb = 0.9 * deal_cost(st, m, best, 1e300);
+    for (int seg : kBatchSegs) {
+        const double t = deal_cost(st, m, seg, tb);
+        if (t < tb) {
+            tb = 0.97 * t;
+            best = seg;
+        }
+    }
+    return best;
 }
 
 // ---- workspace layout -------------------------------------------------------
@@ -692,13 +788,6 @@ int64_t frec_cap(const mp_state* st) {
 size_t frec_bytes(const mp_state* st) { return align_up((size_t)frec_cap(st) * mp::DIAG_VALS * sizeof(double)); }
 double* dev_frec(mp_state* st) { return (double*)((char*)st->ws + ws_frec_off(st)); }
 
-// A batch with an instance of the extended model steps every instance with the general kernels.
-bool batch_gen(const mp_state* st) {
-    for (const Inst& I : st->inst)
-        if (I.ext) return true;
-    return false;
-}
-
 int64_t* dev_ctr(mp_state* st) { return (int64_t*)((char*)st->ws + ws_ctr_off(st)); }
 
 void drop_graphs(mp_state* st) {
@@ -716,7 +805,7 @@ void drop_graphs(mp_state* st) {
 // deals it out.
 void build_items(mp_state* st) {
     st->items.clear();
-    const int seg = batch_seg(st);
+    const int seg = st->item_seg = pick_batch_seg(st);
     for (size_t i = 0; i < st->inst.size(); ++i) {
         const Inst& I = st->inst[i];
         const int nseg = (int)((I.grid.n[1] + seg - 1) / seg);
@@ -745,7 +834,7 @@ double item_cost(const mp_state* st, const Inst& I, int seg, int local) {
 // Deterministic; the results do not depend on the order.
 void arrange_items(mp_state* st, int wpx) {
     const int ninst = (int)st->inst.size();
-    const int seg = batch_seg(st);
+    const int seg = st->item_seg;
     std::vector<std::vector<int>> by_inst(ninst);
     std::vector<double> icost(ninst, 0.0);
     for (int it = 0; it < st->nitems; ++it) {
@@ -788,7 +877,7 @@ void arrange_items(mp_state* st, int wpx) {
 template <typename R>
 int upload_table(mp_state* st) {
     std::vector<mp::InstDesc<R>> tab(st->inst.size());
-    const int seg = batch_seg(st);
+    const int seg = st->item_seg;
     for (size_t i = 0; i < st->inst.size(); ++i) {
         const Inst& I = st->inst[i];
         mp::InstDesc<R>& d = tab[i];
@@ -1720,7 +1809,7 @@ int mp_get_launches(const mp_state* st, int64_t nsteps, int64_t* count, int* bx,
     const Schedule S = schedule(st, nsteps);
     if (count) *count = S.count;
     if (bx) *bx = S.tw > 0 ? S.tw * S.tw : st->bx;
-    if (seg) *seg = S.tw > 0 ? 0 : (st->batch ? batch_seg(st) : launch_seg(st, launch_fuse(st), at_folded(st)));
+    if (seg) *seg = S.tw > 0 ? 0 : (st->batch ? st->item_seg : launch_seg(st, launch_fuse(st), at_folded(st)));
     if (region) *region = S.tw;
     return ok();
 }

@@ -71,3 +71,30 @@ def test_3d_segments_where_a_simd_holds_one_wave(state):
 
     assert seg((256, 256, 256)) == 64
     assert 30 * -(-70 // seg((96, 80, 70))) <= 256
+
+
+@pytest.mark.parametrize("members,side,precision,segs", [
+    # measured within 7 % of the best of 2 .. 32 rows (us per step, 32 rows / best)
+    (24, (128, 400), "f64", (6, 8, 12, 16)),      # 33.9 / 21.9
+    (8, (64, 1024), "f64", (8, 12, 16, 28)),      # 50.0 / 43.4
+    (64, (64, 1024), "f64", (20, 24, 28, 32)),    # 217 / 217
+    (24, (128, 400), "f32", (4, 6, 8)),           # 32.3 / 14.6 (the mean strip's model)
+    (64, (64, 1024), "f32", (24, 28, 32)),        # 127 / 124
+])
+def test_batch_segments_follow_the_deal(state, members, side, precision, segs):
+    rng = np.random.default_rng({(24, 128): 8, (8, 64): 6, (64, 64): 7}[members, side[0]])
+    ps = []
+    for i in range(members):
+        nx, ny = (int(rng.integers(side[0], side[1] + 1)) for _ in range(2))
+        N, K = ((2, 2), (3, 3), (3, 2))[i % 3]
+        p, _, _ = inputs.random_instance(np.random.default_rng(7), 16, 16, N, K, nuclei=1)
+        p = p.copy(n=(nx, ny, 1), precision=precision)
+        p.dt = 0.2 * inputs.dt_limit(p)
+        ps.append(p)
+    st = abi.mp_create_batch(ps)
+    try:
+        assert abi.mp_get_launches(st, 4)[2] in segs
+        abi.mp_set_tile(st, 0, 11, 0)
+        assert abi.mp_get_launches(st, 4) == (2, 256, 11, 0)
+    finally:
+        abi.mp_destroy(st)
