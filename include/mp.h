@@ -270,12 +270,12 @@ int mp_diagnostics_static(const mp_state* st, const void* state_buf, int64_t ste
  * precision allows).  A batched state takes bx = 256 and vec in {-1, 1, 2}
  * (-1 acts as 2).  3D: bx = 256 (32 x 8 tiles) or 512 (64 x 8 tiles, FP32
  * with N + 2 (K - 1) <= 6), seg = z planes per block, vec must be 0 or 1.
- * 0 keeps the current value of a field.  Until seg is given here (or by
- * MP_TILE or mp_tune), a launch on a grid too small to fill the GPU with the
- * default's segments takes shorter ones, and a small 2D grid several steps per
- * launch (mp_step) until any of the three is given; mp_get_tile reports the
- * default, mp_get_launches what is launched.  Results do not depend on the
- * tile shape (bitwise). */
+ * 0 keeps the current value of a field; all three 0 go back to the default.
+ * With the default, and until seg is given here (or by MP_TILE or mp_tune), a
+ * launch on a grid too small to fill the GPU with the default's segments takes
+ * shorter ones, and a small 2D grid several steps per launch (mp_step) until
+ * any of the three is given; mp_get_tile reports the default, mp_get_launches
+ * what is launched.  Results do not depend on the tile shape (bitwise). */
 int mp_set_tile(mp_state* st, int bx, int seg, int vec);
 int mp_get_tile(const mp_state* st, int* bx, int* seg, int* vec);
 
@@ -295,8 +295,11 @@ int mp_get_launches(const mp_state* st, int64_t nsteps, int64_t* count, int* bx,
  * ncand candidates in ``cand``: one untimed launch, then ``reps`` launches
  * from the current buffer into the other one, bracketed by events on
  * ``stream``, and stores the mean milliseconds per step in ms[i] (-1 for a
- * candidate the state rejects).  The current buffer and the time level are
- * untouched; the other buffer is overwritten.  The fastest candidate is set
+ * candidate the state rejects).  A candidate (0, 0, 0, steps per launch) is the
+ * default tile, timed with the launches that a long mp_step makes with it;
+ * mp_tune_candidates lists set tiles only, so add it to keep the default where
+ * it is the fastest.  The current buffer and the time level are untouched; the
+ * other buffer is overwritten.  The fastest candidate is set
  * (as by mp_set_fusion and mp_set_tile) and its index stored in *best.
  * Synchronises ``stream``.  Errors: MP_E_NULLPTR, MP_E_UNBOUND, MP_E_PARAM
  * (ncand < 1, reps < 1 or no valid candidate), MP_E_HIP. */

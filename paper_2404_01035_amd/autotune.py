@@ -1,16 +1,19 @@
 """Tile-shape autotuner for the step kernels, with an on-disk cache.
 
-The library times each candidate -- tile (bx, seg, vec) and steps per launch --
-on the bound state itself (``mp_tune``: launches from the current buffer into
-the other, repeated, with events on the stream) and keeps the fastest per step.  The choice is cached per
-workload signature -- grid, phases, components, precision, potential,
-anisotropy, the extended model, the anti-trapping current's form, batch
-composition and device name -- in a JSON file, so later runs
-of the same workload set the tile without timing.  Results never depend on the
-tile (bitwise), only speed does.
+The library times each candidate -- the default, whose launches pick their
+segment or step small grids several times, and set tiles (bx, seg, vec), with
+each number of steps per launch -- on the bound state itself (``mp_tune``:
+launches from the current buffer into the other, repeated, with events on the
+stream) and keeps the fastest per step.  The choice is cached per workload
+signature -- the library's build, grid, phases, components, precision,
+potential, anisotropy, the extended model, the anti-trapping current's form,
+batch composition and device name -- in a JSON file, so later runs of the same
+workload set the tile without timing.  Results never depend on the tile
+(bitwise), only speed does.
 """
 from __future__ import annotations
 
+import functools
 import hashlib
 import json
 import os
@@ -30,6 +33,13 @@ def default_cache_path() -> str:
     return os.path.join(os.path.expanduser("~"), ".cache", "paper_2404_01035_amd", "tiles.json")
 
 
+@functools.lru_cache(maxsize=None)
+def library_id() -> str:
+    """Hash of the library file: another build's kernels have other best tiles."""
+    with open(abi.LIB_PATH, "rb") as f:
+        return hashlib.sha256(f.read()).hexdigest()[:16]
+
+
 def _extended(p) -> bool:
     """Whether p uses the extended model (the general kernels)."""
     return bool(p.potential == "obstacle_active" or any(
@@ -45,6 +55,7 @@ def signature(plist, device: str, antitrapping: int = 0) -> str:
     (``antitrapping``: the state's mp_get_antitrapping value; it selects other kernels)."""
     p0 = plist[0]
     body = {
+        "library": library_id(),
         "kind": "batch" if len(plist) > 1 else "single",
         "precision": p0.precision,
         "potential": p0.potential,
@@ -81,8 +92,9 @@ def tune(st, plist, stream: int, device: str, reps: int = 10, cache: str | None 
          force: bool = False) -> dict:
     """Pick and set the tile of bound state ``st`` (built from ``plist``).
 
-    Returns {"bx", "seg", "vec", "fuse", "source": "cache" | "timed",
-    "ms": {"bx,seg,vec,fuse": ms per step}}.
+    Returns {"bx", "seg", "vec" (as mp_get_tile reports them), "fuse", "default":
+    whether the default was kept, "source": "cache" | "timed",
+    "ms": {"bx,seg,vec,fuse": ms per step, "0,0,0,fuse" the default's}}.
     """
     path = cache or default_cache_path()
     key = signature(plist, device, abi.mp_get_antitrapping(st))
@@ -90,15 +102,19 @@ def tune(st, plist, stream: int, device: str, reps: int = 10, cache: str | None 
     hit = data.get(key)
     if hit and not force:
         abi.mp_set_fusion(st, hit["fuse"])
-        abi.mp_set_tile(st, hit["bx"], hit["seg"], hit["vec"])
+        abi.mp_set_tile(st, *((0, 0, 0) if hit.get("default") else (hit["bx"], hit["seg"], hit["vec"])))
         return dict(hit, source="cache")
-    cand = abi.mp_tune_candidates(st)
+    tiles = abi.mp_tune_candidates(st)
+    cand = [(0, 0, 0, fuse) for fuse in sorted({c[3] for c in tiles})] + tiles
     ms, best = abi.mp_tune(st, cand, reps, stream)
+    default = cand[best][:3] == (0, 0, 0)
+    bx, seg, vec = abi.mp_get_tile(st) if default else cand[best][:3]
     rec = {
-        "bx": cand[best][0],
-        "seg": cand[best][1],
-        "vec": cand[best][2],
+        "bx": bx,
+        "seg": seg,
+        "vec": vec,
         "fuse": cand[best][3],
+        "default": default,
         "ms": {",".join(map(str, c)): t for c, t in zip(cand, ms)},
     }
     data[key] = rec

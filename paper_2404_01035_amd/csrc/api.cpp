@@ -1211,6 +1211,31 @@ bool d3_tall_ok(const mp_state* st) {
     return 4 * (I.N + 2 * (I.K - 1)) * 66 * 10 * elem <= 64 * 1024;
 }
 
+// The tile of a state for which none was set.
+void default_tile(mp_state* st) {
+    st->vec = -1;
+    st->seg_auto = st->tile_auto = true;
+    if (st->inst[0].grid.dim == 3) {
+        // measured best on 512^3 FP32: 32 x 8 tiles (call_3d has all shapes), long z segments
+        st->bx = 256;
+        st->seg = 64;
+    } else if (st->batch) {
+        // measured best on the 256-instance ensemble (with two steps per launch): one cell
+        // per lane (keeps the batched kernel at 5 waves per SIMD)
+        st->bx = 64 * mp::BATCH_WPB_HOST;
+        st->seg = 32;
+        st->vec = 1;
+    } else {
+        // measured best for two steps per launch on 4096^2: one cell per lane (FP64 at 3
+        // waves per SIMD without spills, FP32 at 5), 31- / 14-row segments
+        // (their wave counts come out just under a whole number of the
+        // chip's resident wave slots, so the last wave round is nearly full)
+        st->bx = 256;
+        st->seg = st->precision == MP_FP64 ? 31 : 14;
+        st->vec = 1;
+    }
+}
+
 void init_state(mp_state* st) {
     st->buf[0] = st->buf[1] = nullptr;
     st->ws = nullptr;
@@ -1230,31 +1255,10 @@ void init_state(mp_state* st) {
     st->aniso = false;
     for (const Inst& I : st->inst) st->aniso = st->aniso || I.aniso;
     st->precision = st->inst[0].prm.precision;
-    st->vec = -1;
-    st->seg_auto = st->tile_auto = true;
     st->potential = kernel_potential(st->inst[0].prm.potential);
-    if (st->inst[0].grid.dim == 3) {
-        // measured best on 512^3 FP32: 32 x 8 tiles (call_3d has all shapes), long z segments
-        st->bx = 256;
-        st->seg = 64;
-    } else if (st->batch) {
-        // measured best on the 256-instance ensemble: two steps per launch,
-        // one cell per lane (keeps the batched kernel at 5 waves per SIMD)
-        st->fuse = 2;
-        st->bx = 64 * mp::BATCH_WPB_HOST;
-        st->seg = 32;
-        st->vec = 1;
-    } else {
-        // two steps per launch (the state crosses HBM once per two steps);
-        // tiles measured best for it on 4096^2: one cell per lane (FP64 at 3
-        // waves per SIMD without spills, FP32 at 5), 31- / 14-row segments
-        // (their wave counts come out just under a whole number of the
-        // chip's resident wave slots, so the last wave round is nearly full)
-        st->fuse = 2;
-        st->bx = 256;
-        st->seg = st->precision == MP_FP64 ? 31 : 14;
-        st->vec = 1;
-    }
+    // two steps per launch in 2D (the state crosses HBM once per two steps)
+    if (st->inst[0].grid.dim == 2) st->fuse = 2;
+    default_tile(st);
 }
 
 // Diagnostics of instance i of the state held in ``base`` (one state buffer),
@@ -1781,14 +1785,18 @@ int mp_set_tile(mp_state* st, int bx, int seg, int vec) {
             return fail(MP_E_PARAM, "unsupported cells per lane %d", vec);
     }
     drop_graphs(st);
-    if (bx || seg || vec) st->tile_auto = false;
+    const bool reset = !bx && !seg && !vec;
+    if (reset)
+        default_tile(st);
+    else
+        st->tile_auto = false;
     if (bx) st->bx = bx;
     if (vec) st->vec = d3 ? -1 : vec;
     if (seg) {
         st->seg = seg;
         st->seg_auto = false;
     }
-    if ((seg || vec) && st->batch) {
+    if ((seg || vec || reset) && st->batch) {
         const int rc = sync_batch(st);
         if (rc) return rc;
     }
@@ -1851,6 +1859,7 @@ int mp_tune(mp_state* st, const int32_t* cand, int ncand, int reps, double* ms, 
     hipStream_t s = (hipStream_t)stream;
     const int bx0 = st->bx, seg0 = st->seg, vec0 = st->vec, fuse0 = st->fuse;
     const bool seg_auto0 = st->seg_auto, tile_auto0 = st->tile_auto;
+    constexpr int64_t run = 100;  // the default candidate's launches are those of a run of this many steps
     hipEvent_t e[2] = {nullptr, nullptr};
     int rc = hip_check(hipEventCreate(&e[0]), "hipEventCreate");
     if (rc == MP_OK) rc = hip_check(hipEventCreate(&e[1]), "hipEventCreate");
@@ -1861,7 +1870,8 @@ int mp_tune(mp_state* st, const int32_t* cand, int ncand, int reps, double* ms, 
         if (mp_set_fusion(st, c[3]) != MP_OK) continue;
         if (mp_set_tile(st, c[0], c[1], c[2]) != MP_OK) continue;
         mp::KernelCall k;
-        if (make_step_call(st, 0, st->cur, k, launch_fuse(st)) != MP_OK) continue;
+        const Schedule S = schedule(st, run);
+        if (make_step_call(st, 0, st->cur, k, S.steps(0), S.tw) != MP_OK) continue;
         rc = launch(k, s);
         if (rc == MP_OK) rc = hip_check(hipEventRecord(e[0], s), "hipEventRecord");
         for (int r = 0; r < reps && rc == MP_OK; ++r) rc = launch(k, s);
@@ -1870,17 +1880,19 @@ int mp_tune(mp_state* st, const int32_t* cand, int ncand, int reps, double* ms, 
         float t = 0.0f;
         if (rc == MP_OK) rc = hip_check(hipEventElapsedTime(&t, e[0], e[1]), "hipEventElapsedTime");
         if (rc != MP_OK) break;
-        ms[i] = (double)t / reps / launch_fuse(st);
+        ms[i] = (double)t / reps / S.steps(0);
         if (bi < 0 || ms[i] < ms[bi]) bi = i;
     }
     for (hipEvent_t x : e)
         if (x) (void)hipEventDestroy(x);
     if (rc != MP_OK || bi < 0) {
         const std::string why = rc != MP_OK ? g_err : std::string("no valid tile candidate");
-        (void)mp_set_fusion(st, fuse0);
-        (void)mp_set_tile(st, bx0, seg0, vec0);
+        st->bx = bx0;
+        st->seg = seg0;
+        st->vec = vec0;
         st->seg_auto = seg_auto0;
         st->tile_auto = tile_auto0;
+        (void)mp_set_fusion(st, fuse0);
         if (st->batch) (void)sync_batch(st);
         return fail(rc != MP_OK ? rc : MP_E_PARAM, "mp_tune: %s", why.c_str());
     }

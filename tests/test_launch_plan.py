@@ -98,3 +98,30 @@ def test_batch_segments_follow_the_deal(state, members, side, precision, segs):
         assert abi.mp_get_launches(st, 4) == (2, 256, 11, 0)
     finally:
         abi.mp_destroy(st)
+
+
+@pytest.mark.parametrize("make", [
+    lambda: abi.mp_create(inputs.config_c1()[0]),
+    lambda: abi.mp_create(inputs.eutectic_params(n=(1024, 768, 1), precision="f32")),
+    lambda: abi.mp_create(inputs.dendrite_params(n=(96, 80, 70))),
+    lambda: abi.mp_create_batch([m[0] for m in inputs.config_c4(ninst=3, side=(64, 90))]),
+])
+def test_all_zero_goes_back_to_the_default_tile(make):
+    st = make()
+    try:
+        tile, launches = abi.mp_get_tile(st), abi.mp_get_launches(st, 40)
+        abi.mp_set_tile(st, 0, 9, 1)
+        assert abi.mp_get_launches(st, 40) != launches
+        abi.mp_set_tile(st, 0, 0, 0)
+        assert (abi.mp_get_tile(st), abi.mp_get_launches(st, 40)) == (tile, launches)
+    finally:
+        abi.mp_destroy(st)
+
+
+def test_tuned_tiles_belong_to_one_build(monkeypatch):
+    from paper_2404_01035_amd import autotune
+
+    p = inputs.config_c1()[0]
+    a = autotune.signature([p], "dev")
+    monkeypatch.setattr(autotune, "library_id", lambda: "another build")
+    assert autotune.signature([p], "dev") != a
