@@ -956,8 +956,7 @@ constexpr TileModel kTileModels[] = {{16, 0.6, 0.16}, {24, 2.1, 0.40}, {32, 2.5,
 constexpr double kTileBase = 5.4;
 constexpr int kTileLeast = 3;  // fewer steps per launch: the strips' two are as good
 
-// parity: the schedule must make as many launches as the strips, modulo 2.
-Schedule schedule(const mp_state* st, int64_t n, bool parity = true) {
+Schedule schedule(const mp_state* st, int64_t n) {
     const int F = launch_fuse(st);
     Schedule S{n, (n + F - 1) / F, 0, F};
     if (st->batch || st->antitrap || st->fuse != 2 || !st->tile_auto || st->inst[0].grid.dim != 2) return S;
@@ -970,7 +969,7 @@ Schedule schedule(const mp_state* st, int64_t n, bool parity = true) {
     for (const TileModel& m : kTileModels)
         for (int T = kTileLeast; 2 * T < m.tw && T <= n; ++T) {
             int64_t c = (n + T - 1) / T;
-            if (parity) c += (c ^ strips) & 1;
+            c += (c ^ strips) & 1;
             const int most = (int)((n + c - 1) / c);
             if (n / c < kTileLeast) continue;
             const int ow = m.tw - 2 * most;
@@ -1052,7 +1051,7 @@ int sync_batch(mp_state* st) {
 
 int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr, int kstep,
                      mp::KernelCall& k, int fuse = 1, void* out1 = nullptr, const mp::DiagOut* diag = nullptr,
-                     int tw = 0, int64_t out1stride = 0);
+                     int tw = 0);
 
 
 // One launch of `fuse` steps (tw > 0: by the tile kernel); kstep is the
@@ -1087,7 +1086,7 @@ constexpr double kCachedBytes = 256.0 * 1024 * 1024;
 // Single-grid launch of `fuse` steps from ``in`` to ``out`` at time level
 // *ctr + kstep.
 int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr, int kstep,
-                     mp::KernelCall& k, int fuse, void* out1, const mp::DiagOut* diag, int tw, int64_t out1stride) {
+                     mp::KernelCall& k, int fuse, void* out1, const mp::DiagOut* diag, int tw) {
     const Inst& I = st->inst[0];
     mp::StepLaunch L;
     L.in = in;
@@ -1108,7 +1107,6 @@ int make_single_call(mp_state* st, const void* in, void* out, const int64_t* ctr
     L.kstep = kstep;
     L.diag = diag;
     L.tw = tw;
-    L.out1stride = out1stride;
     temperature_law(I, L.tb0, L.tdn, L.tslope);
     if (tw > 0) {
         if (st->precision == MP_FP64) {
@@ -2055,26 +2053,22 @@ int mp_adjoint(mp_state* st, const void* ckpt_buf, int64_t nsteps, int64_t every
     auto len_of = [&](int64_t k) { return (nsteps - k * every) < every ? (nsteps - k * every) : every; };
     // Segment k's states, restored from checkpoint k and recomputed into
     // buffer k mod 2, on stream q.
-    // Several steps per launch where the kernel can also store the states
-    // between them (the tile kernel; the strips' two at one cell per lane),
-    // else one.
+    // Two steps per launch where the kernel can also store the state between
+    // them (the strips at one cell per lane), else one.  Not by the tile kernel:
+    // it fills idle lanes with rim cells stepped again, and here the sweep of the
+    // other segment has those lanes.  Measured, sweep with recomputation, us per
+    // step, tiles / strips: FP32 64^2 8.4 / 8.2, 256^2 9.9 / 9.4, 512^2 17.4 / 16.8,
+    // FP64 64^2 9.5 / 9.3, 256^2 13.5 / 13.5, 512^2 26.3 / 26.3.
     auto recompute = [&](int64_t k, hipStream_t q) {
         char* seg = w + L.seg[k & 1];
         auto at = [&](int64_t i) { return seg + (size_t)i * L.state; };
         int r = hip_check(hipMemcpyAsync(seg, (const char*)ckpt_buf + (size_t)k * L.state, sb,
                                          hipMemcpyDeviceToDevice, q),
                           "checkpoint restore");
-        const Schedule S = schedule(st, len_of(k) - 1, false);
-        for (int64_t i = 0, j = 0; r == MP_OK && i + 1 < len_of(k);) {
+        for (int64_t i = 0; r == MP_OK && i + 1 < len_of(k);) {
             const int kstep = (int)(n0 + k * every + i);
             mp::KernelCall kc;
-            if (S.tw > 0) {
-                const int T = S.steps(j++);
-                r = make_single_call(st, at(i), at(i + T), zctr, kstep, kc, T, T > 1 ? at(i + 1) : nullptr, nullptr,
-                                     S.tw, (int64_t)(L.state / elem_of(st->precision)));
-                if (r) return fail(r, "no kernel instance for this configuration");
-                i += T;
-            } else if (i + 2 < len_of(k) && make_single_call(st, at(i), at(i + 2), zctr, kstep, kc, 2, at(i + 1)) == MP_OK) {
+            if (i + 2 < len_of(k) && make_single_call(st, at(i), at(i + 2), zctr, kstep, kc, 2, at(i + 1)) == MP_OK) {
                 i += 2;
             } else {
                 r = make_single_call(st, at(i), at(i + 1), zctr, kstep, kc);

@@ -93,7 +93,6 @@ struct StepLaunch {
     int fuse;  // steps per launch: 1, or 2 (2D single grid), or more (tiles)
     int tw = 0;  // > 0: the 2D tile kernel on regions of tw x tw cells
     bool nt = false;  // 3D: store the new state past the caches
-    int64_t out1stride = 0;  // tiles: elements between the states stored at out1 (after steps 1 .. fuse - 1)
     const int64_t* stepctr;
     int kstep;
     double tb0, tdn, tslope;

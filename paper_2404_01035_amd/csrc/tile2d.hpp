@@ -24,10 +24,9 @@
 namespace mp {
 
 template <typename R, int NP, int NM, bool ANISO, bool OBST, bool GEN, int TW>
-__device__ __forceinline__ void tile2d_block(const R* __restrict__ in, R* __restrict__ out, R* __restrict__ mid,
-                                             int64_t midstride, const Geom& g, const Coef<R>& c, double tb0,
-                                             double tdn, double tslope, double n, int T, int ntx,
-                                             const CoefX<R>* x) {
+__device__ __forceinline__ void tile2d_block(const R* __restrict__ in, R* __restrict__ out, const Geom& g,
+                                             const Coef<R>& c, double tb0, double tdn, double tslope, double n,
+                                             int T, int ntx, const CoefX<R>* x) {
     constexpr int NF = NP + NM;
     constexpr int NMM = mob_n<NM, GEN>();
     constexpr int NC = TW * TW;
@@ -128,13 +127,6 @@ __device__ __forceinline__ void tile2d_block(const R* __restrict__ in, R* __rest
 #pragma unroll
             for (int k = 0; k < NM; ++k) mu[k] = un[k];
             mobility_any<R, NP, NM, GEN>(h, c, x, Mt);
-            if (mid && s < T && mine) {
-                R* q = mid + (s - 1) * midstride;
-#pragma unroll
-                for (int a = 0; a < NP; ++a) q[a * g.fstride + o] = phi[a];
-#pragma unroll
-                for (int k = 0; k < NM; ++k) q[(NP + k) * g.fstride + o] = mu[k];
-            }
         }
     }
     if (mine) {
@@ -147,19 +139,18 @@ __device__ __forceinline__ void tile2d_block(const R* __restrict__ in, R* __rest
 
 template <typename R, int NP, int NM, bool ANISO, bool OBST, int TW>
 __global__ void __launch_bounds__(TW * TW)
-k_tile2d(const R* __restrict__ in, R* __restrict__ out, R* __restrict__ mid, int64_t midstride, Geom g, Coef<R> c,
-         const int64_t* __restrict__ stepctr, int kstep, double tb0, double tdn, double tslope, int T, int ntx) {
-    tile2d_block<R, NP, NM, ANISO, OBST, false, TW>(in, out, mid, midstride, g, c, tb0, tdn, tslope,
-                                                    (double)(*stepctr + kstep), T, ntx, nullptr);
+k_tile2d(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c, const int64_t* __restrict__ stepctr,
+         int kstep, double tb0, double tdn, double tslope, int T, int ntx) {
+    tile2d_block<R, NP, NM, ANISO, OBST, false, TW>(in, out, g, c, tb0, tdn, tslope, (double)(*stepctr + kstep), T,
+                                                    ntx, nullptr);
 }
 
 template <typename R, int NP, int NM, bool ANISO, bool OBST, int TW>
 __global__ void __launch_bounds__(TW * TW)
-k_tile2d_gen(const R* __restrict__ in, R* __restrict__ out, R* __restrict__ mid, int64_t midstride, Geom g,
-             Coef<R> c, const int64_t* __restrict__ stepctr, int kstep, double tb0, double tdn, double tslope, int T,
-             int ntx, CoefX<R> x) {
-    tile2d_block<R, NP, NM, ANISO, OBST, true, TW>(in, out, mid, midstride, g, c, tb0, tdn, tslope,
-                                                   (double)(*stepctr + kstep), T, ntx, &x);
+k_tile2d_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c, const int64_t* __restrict__ stepctr,
+             int kstep, double tb0, double tdn, double tslope, int T, int ntx, CoefX<R> x) {
+    tile2d_block<R, NP, NM, ANISO, OBST, true, TW>(in, out, g, c, tb0, tdn, tslope, (double)(*stepctr + kstep), T,
+                                                   ntx, &x);
 }
 
 // One launch of L.fuse steps on regions of TW x TW cells.
@@ -178,8 +169,6 @@ int call_tile_w(const StepLaunch& L, const Coef<R>& c, const CoefX<R>* x, Kernel
     k.block = dim3(TW * TW);
     k.arg((const R*)L.in);
     k.arg((R*)L.out);
-    k.arg((R*)L.out1);
-    k.arg(L.out1stride);
     k.arg(L.g);
     k.arg(c);
     k.arg(L.stepctr);
