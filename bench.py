@@ -59,27 +59,27 @@ CSRC = os.path.join(ROOT, "paper_2404_01035_amd", "csrc")
 # it was taken on (LEG_SOURCES); otherwise the leg reports traffic null.
 TRAFFIC = {
     # profiles/counters_all_legs.md
-    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "b9ef6632a5390fc3",
+    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "21defa7f9193e95e",
         "bytes": (2.0 * 364888.8 + 661119.2) * 1024},
-    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "51fc0ee2e4f1b8d6",
+    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "60bc039f042ca1c5",
         "bytes": (2.0 * 192162.5 + 331619.1) * 1024},
-    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "ea853707ed8b3dab",
+    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "3a74e1aeae256bde",
         "bytes": (2.0 * 384631.9 + 655914.3) * 1024},
-    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "c50eec2280947b30",
+    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "8d71403240440108",
         "bytes": (2.0 * 224288.2 + 328204.2) * 1024},
-    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "4dba722c9cc72a9c",
+    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "8c3187a8689254a5",
         "bytes": (2.0 * 962720.0 + 1572864.0) * 1024},
-    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "0b7b1f322b3cffbf",
+    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "dd86e8c448a70ffd",
         "bytes": (2.0 * 396150.6 + 669848.1) * 1024},
-    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "0b7b1f322b3cffbf",
+    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "dd86e8c448a70ffd",
         "bytes": (2.0 * 223953.6 + 335382.8) * 1024},
-    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "24f83c952a5f954a",
+    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "8929344579ddcb91",
         "bytes": (2.0 * 869517.2 + 270024.5) * 1024},
-    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "24f83c952a5f954a",
+    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "8929344579ddcb91",
         "bytes": (2.0 * 462333.6 + 140322.1) * 1024},
-    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "aa3a2ce7385d7705",
+    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "9d5157f2fd155a49",
         "bytes": (2.0 * 2063437.2 + 578066.0) * 1024},
-    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "3b2d56e1294f557f",
+    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "e8993237cfe51931",
         "bytes": (2.0 * 698678.5 + 1204579.6) * 1024},
 }
 METRIC = "cell-updates/s of fused phi+mu step (FP64 vs FP32), % HBM peak, adjoint/fwd cost"
@@ -221,17 +221,17 @@ def alu_roofline(flops_per_step, ms_step, precision, traffic=None):
 # peaks above: 16 FP64 or 32 FP32 lanes per SIMD per cycle).
 VALU = {
     # profiles/counters_all_legs.md
-    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "b9ef6632a5390fc3", "insts": 153459252.0},
-    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "51fc0ee2e4f1b8d6", "insts": 137889195.0},
-    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "ea853707ed8b3dab", "insts": 195920541.0},
-    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "c50eec2280947b30", "insts": 169620984.0},
-    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "4dba722c9cc72a9c", "insts": 551390957.0},
-    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "0b7b1f322b3cffbf", "insts": 135827199.0},
-    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "0b7b1f322b3cffbf", "insts": 120842193.0},
-    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "24f83c952a5f954a", "insts": 65303901.0},
-    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "24f83c952a5f954a", "insts": 51761928.0},
-    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "aa3a2ce7385d7705", "insts": 455707580.0},
-    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "3b2d56e1294f557f", "insts": 443575096.0},
+    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "21defa7f9193e95e", "insts": 153459252.0},
+    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "60bc039f042ca1c5", "insts": 137889195.0},
+    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "3a74e1aeae256bde", "insts": 195920541.0},
+    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "8d71403240440108", "insts": 169620984.0},
+    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "8c3187a8689254a5", "insts": 551390957.0},
+    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "dd86e8c448a70ffd", "insts": 135827199.0},
+    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "dd86e8c448a70ffd", "insts": 120842193.0},
+    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "8929344579ddcb91", "insts": 65303901.0},
+    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "8929344579ddcb91", "insts": 51761928.0},
+    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "9d5157f2fd155a49", "insts": 455707580.0},
+    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "e8993237cfe51931", "insts": 443575096.0},
 }
 VALU_CYCLES = {"f64": 4, "f32": 2}
 SIMDS = 1024         # 256 CUs x 4 SIMDs

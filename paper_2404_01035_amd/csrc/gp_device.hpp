@@ -138,6 +138,28 @@ __device__ __forceinline__ const T& fresh(KernArg<T> p) {
     return *(const T*)p;
 }
 
+// The argument of type T of a kernel of type F, where it lies: arguments follow
+// each other in order, each at the next multiple of its alignment.
+template <typename T, typename F>
+struct KernArgAt;
+template <typename T, typename... A>
+struct KernArgAt<T, void (*)(A...)> {
+    static constexpr int count = (0 + ... + (int)std::is_same_v<T, A>);
+    static_assert(count == 1, "one argument of the type");
+    static constexpr size_t offset() {
+        size_t end = 0, at = 0;
+        ((end = (end + alignof(A) - 1) / alignof(A) * alignof(A), at = std::is_same_v<T, A> ? end : at,
+          end += sizeof(A)),
+         ...);
+        return at;
+    }
+};
+template <typename T, typename F>
+__device__ __forceinline__ KernArg<T> kern_arg() {
+    typedef const __attribute__((address_space(4))) char Byte;
+    return (KernArg<T>)((Byte*)__builtin_amdgcn_kernarg_segment_ptr() + KernArgAt<T, F>::offset());
+}
+
 template <typename R, bool KA>
 struct CoefSrc;
 template <typename R>

@@ -691,23 +691,13 @@ k_step2d_x2(const R* __restrict__ in, R* __restrict__ out, R* __restrict__ out1,
 
 // The general kernels of the extended model (one cell per lane): the same
 // strips with the GEN cell and face arithmetic, and the extended
-// coefficients as a further argument; both read again at every use (CoefSrc).
-template <typename R>
-struct StripGenArgs {  // the kernels' arguments as they lie in memory
-    const R* in;
-    R* out;
-    Geom g;
-    Coef<R> c;
-    const int64_t* stepctr;
-    int kstep;
-    double tb0, tdn, tslope;
-    int seg, ntx, nseg;
-    CoefX<R> x;
-};
-template <typename R>
-__device__ __forceinline__ CoefSrc<R, true> strip_gen_coef() {
-    const KernArg<StripGenArgs<R>> a = (KernArg<StripGenArgs<R>>)__builtin_amdgcn_kernarg_segment_ptr();
-    return {&a->c, &a->x};
+// coefficients as a further argument.
+template <typename R, typename F, bool KA>
+__device__ __forceinline__ CoefSrc<R, KA> strip_gen_coef(const Coef<R>& c, const CoefX<R>& x) {
+    if constexpr (KA)
+        return {kern_arg<Coef<R>, F>(), kern_arg<CoefX<R>, F>()};
+    else
+        return {c, &x};
 }
 
 template <typename R, int NP, int NM, bool ANISO, bool OBST>
@@ -722,8 +712,9 @@ k_step2d_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
-    strip2d<R, NP, NM, ANISO, OBST, 1, W2D_LANES_OUT, true>(in, out, g, strip_gen_coef<R>(), tbase,
-                                                                          tslope, tx, m0, min(m0 + seg, g.ny));
+    const auto q = strip_gen_coef<R, decltype(&k_step2d_gen<R, NP, NM, ANISO, OBST>), true>(c, x);
+    strip2d<R, NP, NM, ANISO, OBST, 1, W2D_LANES_OUT, true>(in, out, g, q, tbase, tslope, tx, m0,
+                                                            min(m0 + seg, g.ny));
 }
 
 template <typename R, int NP, int NM, bool ANISO, bool OBST>
@@ -738,7 +729,7 @@ k_step2d_x2_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double n = (double)(*stepctr + kstep);
-    const CoefSrc<R, true> q = strip_gen_coef<R>();
+    const auto q = strip_gen_coef<R, decltype(&k_step2d_x2_gen<R, NP, NM, ANISO, OBST>), true>(c, x);
     bool fixL, fixR;
     x2_column<1>(g, x2_first_col<1>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)

@@ -280,20 +280,20 @@ __device__ __forceinline__ void strip2d_at(const R* __restrict__ in, R* __restri
     put(m1 - 1);
 }
 
-// The folded kernels' arguments as they lie in memory (x: the general kernel's only).
-template <typename R>
-struct StripAtArgs {
-    const R* in;
-    R* out;
-    Geom g;
-    Coef<R> c;
-    AtCoef<R> ac;
-    const int64_t* stepctr;
-    int kstep;
-    double tb0, tdn, tslope;
-    int seg, ntx, nseg;
-    CoefX<R> x;
-};
+template <typename R, typename F, bool KA>
+__device__ __forceinline__ CoefSrc<R, KA> strip_coef(const Coef<R>& c) {
+    if constexpr (KA)
+        return {kern_arg<Coef<R>, F>(), nullptr};
+    else
+        return {c, nullptr};
+}
+template <typename R, typename F, bool KA>
+__device__ __forceinline__ AtSrc<R, KA> strip_at_coef(const AtCoef<R>& ac) {
+    if constexpr (KA)
+        return {kern_arg<AtCoef<R>, F>()};
+    else
+        return {ac};
+}
 
 template <typename R, int NP, int NM, bool ANISO, bool OBST>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(MP_WAVES_PER_EU)))
@@ -307,9 +307,9 @@ k_step2d_at(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c, At
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
-    const KernArg<StripAtArgs<R>> ka = (KernArg<StripAtArgs<R>>)__builtin_amdgcn_kernarg_segment_ptr();
-    const CoefSrc<R, true> q{&ka->c, nullptr};
-    const AtSrc<R, true> as{&ka->ac};
+    typedef decltype(&k_step2d_at<R, NP, NM, ANISO, OBST>) F;
+    const auto q = strip_coef<R, F, true>(c);
+    const auto as = strip_at_coef<R, F, true>(ac);
     bool fixL, fixR;
     x2_column<1>(g, x2_first_col<1>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)
@@ -332,9 +332,9 @@ k_step2d_at_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
-    const KernArg<StripAtArgs<R>> ka = (KernArg<StripAtArgs<R>>)__builtin_amdgcn_kernarg_segment_ptr();
-    const CoefSrc<R, true> q{&ka->c, &ka->x};
-    const AtSrc<R, true> as{&ka->ac};
+    typedef decltype(&k_step2d_at_gen<R, NP, NM, ANISO, OBST>) F;
+    const auto q = strip_gen_coef<R, F, true>(c, x);
+    const auto as = strip_at_coef<R, F, true>(ac);
     bool fixL, fixR;
     x2_column<1>(g, x2_first_col<1>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)
