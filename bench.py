@@ -59,27 +59,27 @@ CSRC = os.path.join(ROOT, "paper_2404_01035_amd", "csrc")
 # it was taken on (LEG_SOURCES); otherwise the leg reports traffic null.
 TRAFFIC = {
     # profiles/counters_all_legs.md
-    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "21defa7f9193e95e",
+    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "832af8acb760dacb",
         "bytes": (2.0 * 364888.8 + 661119.2) * 1024},
-    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "60bc039f042ca1c5",
+    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "bec153e13de6137d",
         "bytes": (2.0 * 192162.5 + 331619.1) * 1024},
-    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "3a74e1aeae256bde",
+    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "77b9a9619bdeb9e6",
         "bytes": (2.0 * 384631.9 + 655914.3) * 1024},
-    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "8d71403240440108",
+    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "26362ccec458874a",
         "bytes": (2.0 * 224288.2 + 328204.2) * 1024},
-    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "8c3187a8689254a5",
+    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "5e237a348fba0e86",
         "bytes": (2.0 * 962720.0 + 1572864.0) * 1024},
-    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "dd86e8c448a70ffd",
+    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "97f1e1a1de67b494",
         "bytes": (2.0 * 396150.6 + 669848.1) * 1024},
-    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "dd86e8c448a70ffd",
+    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "97f1e1a1de67b494",
         "bytes": (2.0 * 223953.6 + 335382.8) * 1024},
-    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "8929344579ddcb91",
+    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "585053eecbdecca7",
         "bytes": (2.0 * 869517.2 + 270024.5) * 1024},
-    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "8929344579ddcb91",
+    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "585053eecbdecca7",
         "bytes": (2.0 * 462333.6 + 140322.1) * 1024},
-    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "9d5157f2fd155a49",
+    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "fc4ba9d71f887dd5",
         "bytes": (2.0 * 2063437.2 + 578066.0) * 1024},
-    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "e8993237cfe51931",
+    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "116ea4717ef83445",
         "bytes": (2.0 * 698678.5 + 1204579.6) * 1024},
 }
 METRIC = "cell-updates/s of fused phi+mu step (FP64 vs FP32), % HBM peak, adjoint/fwd cost"
@@ -221,17 +221,17 @@ def alu_roofline(flops_per_step, ms_step, precision, traffic=None):
 # peaks above: 16 FP64 or 32 FP32 lanes per SIMD per cycle).
 VALU = {
     # profiles/counters_all_legs.md
-    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "21defa7f9193e95e", "insts": 153459252.0},
-    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "60bc039f042ca1c5", "insts": 137889195.0},
-    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "3a74e1aeae256bde", "insts": 195920541.0},
-    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "8d71403240440108", "insts": 169620984.0},
-    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "8c3187a8689254a5", "insts": 551390957.0},
-    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "dd86e8c448a70ffd", "insts": 135827199.0},
-    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "dd86e8c448a70ffd", "insts": 120842193.0},
-    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "8929344579ddcb91", "insts": 65303901.0},
-    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "8929344579ddcb91", "insts": 51761928.0},
-    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "9d5157f2fd155a49", "insts": 455707580.0},
-    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "e8993237cfe51931", "insts": 443575096.0},
+    "c2_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "832af8acb760dacb", "insts": 153459252.0},
+    "c2_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "bec153e13de6137d", "insts": 137889195.0},
+    "c2ext_f64": {"tile": [256, 31, 1], "fuse": 2, "src": "77b9a9619bdeb9e6", "insts": 195920541.0},
+    "c2ext_f32": {"tile": [256, 14, 1], "fuse": 2, "src": "26362ccec458874a", "insts": 169620984.0},
+    "c3": {"tile": [256, 64, -1], "fuse": 1, "src": "5e237a348fba0e86", "insts": 551390957.0},
+    "atf_f64": {"tile": [256, 31, 1], "fuse": 1, "src": "97f1e1a1de67b494", "insts": 135827199.0},
+    "atf_f32": {"tile": [256, 14, 1], "fuse": 1, "src": "97f1e1a1de67b494", "insts": 120842193.0},
+    "at_f64": {"tile": [62, 12, 1], "fuse": 1, "src": "585053eecbdecca7", "insts": 65303901.0},
+    "at_f32": {"tile": [62, 12, 1], "fuse": 1, "src": "585053eecbdecca7", "insts": 51761928.0},
+    "at3d_f32": {"tile": [62, 2, 1], "fuse": 1, "src": "fc4ba9d71f887dd5", "insts": 455707580.0},
+    "c4": {"tile": [256, 32, 1], "fuse": 2, "src": "116ea4717ef83445", "insts": 443575096.0},
 }
 VALU_CYCLES = {"f64": 4, "f32": 2}
 SIMDS = 1024         # 256 CUs x 4 SIMDs

@@ -123,10 +123,14 @@ __device__ __forceinline__ void store_cell(R* __restrict__ out, int64_t fs, int6
 // lanes of vector registers and fetches with v_readlane, a slot of the vector
 // unit at every use: 227 of the 909 vector instructions of two rows of the
 // general FP64 kernel, 160 of 1173 of a row with the anti-trapping current.
-// Reading them again costs scalar loads from cached constant memory instead.
-// Measured: general FP64 kernel, eutectic with slopes 2048 x 1536, 457 -> 438
-// us per ten steps of the public call.  Not worth it where few are parked: the
-// plain FP64 kernel and FP32 lose nothing to it and gain nothing.
+// Reading them again costs scalar loads from cached constant memory instead, and
+// their latency.  reread_coef says where that is the better: the general and the
+// anti-trapping 2D kernels of three phases and two mu fields.  Measured, us per
+// step, read once / again: 3000 x 2000 general two-step FP64 92.4 / 88.1, with
+// the current FP64 178 / 170, both 243 / 193, FP32 96.6 / 94.2; but with fewer
+// fields general two-step FP64 38.4 / 40.0 (2 + 1) and 56.2 / 58.4 (2 + 2), FP32
+// anisotropic 55.9 / 60.7 (3 + 1), with the current FP32 57.4 / 61.0 (2 + 1).
+// The plain kernels lose nothing to it and gain nothing.
 // The empty asm hides where the pointer came from, which keeps the loads inside
 // the loop and each use's registers to itself.
 template <typename T>
@@ -136,6 +140,11 @@ template <typename T>
 __device__ __forceinline__ const T& fresh(KernArg<T> p) {
     asm volatile("" : "+s"(p));
     return *(const T*)p;
+}
+
+template <int NP, int NM>
+constexpr bool reread_coef() {
+    return NP + NM == 5;
 }
 
 // The argument of type T of a kernel of type F, where it lies: arguments follow

@@ -712,7 +712,7 @@ k_step2d_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c,
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
-    const auto q = strip_gen_coef<R, decltype(&k_step2d_gen<R, NP, NM, ANISO, OBST>), true>(c, x);
+    const auto q = strip_gen_coef<R, decltype(&k_step2d_gen<R, NP, NM, ANISO, OBST>), reread_coef<NP, NM>()>(c, x);
     strip2d<R, NP, NM, ANISO, OBST, 1, W2D_LANES_OUT, true>(in, out, g, q, tbase, tslope, tx, m0,
                                                             min(m0 + seg, g.ny));
 }
@@ -729,7 +729,7 @@ k_step2d_x2_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c
     const int sg = wid / ntx;
     const int m0 = sg * seg;
     const double n = (double)(*stepctr + kstep);
-    const auto q = strip_gen_coef<R, decltype(&k_step2d_x2_gen<R, NP, NM, ANISO, OBST>), true>(c, x);
+    const auto q = strip_gen_coef<R, decltype(&k_step2d_x2_gen<R, NP, NM, ANISO, OBST>), reread_coef<NP, NM>()>(c, x);
     bool fixL, fixR;
     x2_column<1>(g, x2_first_col<1>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)

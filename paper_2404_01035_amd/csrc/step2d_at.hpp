@@ -308,8 +308,8 @@ k_step2d_at(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c, At
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
     typedef decltype(&k_step2d_at<R, NP, NM, ANISO, OBST>) F;
-    const auto q = strip_coef<R, F, true>(c);
-    const auto as = strip_at_coef<R, F, true>(ac);
+    const auto q = strip_coef<R, F, reread_coef<NP, NM>()>(c);
+    const auto as = strip_at_coef<R, F, reread_coef<NP, NM>()>(ac);
     bool fixL, fixR;
     x2_column<1>(g, x2_first_col<1>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)
@@ -333,8 +333,10 @@ k_step2d_at_gen(const R* __restrict__ in, R* __restrict__ out, Geom g, Coef<R> c
     const int m0 = sg * seg;
     const double tbase = tb0 + tdn * (double)(*stepctr + kstep);
     typedef decltype(&k_step2d_at_gen<R, NP, NM, ANISO, OBST>) F;
-    const auto q = strip_gen_coef<R, F, true>(c, x);
-    const auto as = strip_at_coef<R, F, true>(ac);
+    // (FP64 with two mu fields: also with two phases, 3000 x 2000 139.4 read once, 134.9 again)
+    constexpr bool again = reread_coef<NP, NM>() || (sizeof(R) == 8 && NM == 2);
+    const auto q = strip_gen_coef<R, F, again>(c, x);
+    const auto as = strip_at_coef<R, F, again>(ac);
     bool fixL, fixR;
     x2_column<1>(g, x2_first_col<1>(tx, threadIdx.x & 63), fixL, fixR);
     if (__ballot(fixL || fixR) != 0)
