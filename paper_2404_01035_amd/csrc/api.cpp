@@ -956,6 +956,23 @@ constexpr TileModel kTileModels[] = {{16, 0.6, 0.16}, {24, 2.1, 0.40}, {32, 2.5,
 constexpr double kTileBase = 5.4;
 constexpr int kTileLeast = 3;  // fewer steps per launch: the strips' two are as good
 
+// A cell's work in the tile kernel beside what q says.  A thread evaluates all
+// four faces of its cell, the strips two, so costly faces weigh more:
+// anisotropic ones, most with three phases, and where FP64 regions of 32 x 32
+// are held to 128 registers per thread and spill (up to 30 VGPRs plain, 47
+// general); and the two mu fields' matrix products of the general kernel with
+// two phases.  From 448 configurations of 64^2 to 1024^2, 24 steps, us per step
+// of tiles / strips: without it 36 of them took tiles that were over 3 % slower,
+// at worst 512^2 FP64 N = 3, K = 2 anisotropic 15.6 / 10.7, 400 x 300 FP64 N = K = 3
+// anisotropic general 15.1 / 11.5, 768 x 640 FP32 N = K = 3 anisotropic 13.9 / 11.3;
+// with it 6, at worst 14 %.
+double tile_work(const Inst& I, bool f64, int tw) {
+    if (!I.aniso) return I.ext && I.N == 2 && I.K == 3 ? 1.25 : 1.0;
+    if (I.N == 2) return 1.15;
+    if (!f64) return I.ext ? 1.2 : 1.5;
+    return I.ext ? 1.55 : (tw == 32 ? 1.9 : 1.35);
+}
+
 Schedule schedule(const mp_state* st, int64_t n) {
     const int F = launch_fuse(st);
     Schedule S{n, (n + F - 1) / F, 0, F};
@@ -975,7 +992,8 @@ Schedule schedule(const mp_state* st, int64_t n) {
             const int ow = m.tw - 2 * most;
             const int64_t blocks = ((g.n[0] + ow - 1) / ow) * ((g.n[1] + ow - 1) / ow);
             const double lds = 2.0 * elem * m.tw * m.tw * (I.N + nm + (I.ext ? nm * nm : nm));
-            const double q = cell_work(I) * (elem == 4.0 ? 1.0 : (lds > 80.0 * 1024.0 ? 1.9 : 1.45));
+            const double q =
+                tile_work(I, elem == 8.0, m.tw) * cell_work(I) * (elem == 4.0 ? 1.0 : (lds > 80.0 * 1024.0 ? 1.9 : 1.45));
             const double r = (double)((blocks + kChipCus - 1) / kChipCus);
             const double t = (double)c * (kTileBase + r * q * (m.a + m.b * most));
             if (t < best) {

@@ -125,3 +125,24 @@ def test_tuned_tiles_belong_to_one_build(monkeypatch):
     a = autotune.signature([p], "dev")
     monkeypatch.setattr(autotune, "library_id", lambda: "another build")
     assert autotune.signature([p], "dev") != a
+
+
+@pytest.mark.parametrize("n,N,K,precision,aniso,ext,tiles", [
+    # measured with 24 steps, us per step of the tile kernel / the strips
+    ((512, 512), 3, 2, "f64", True, False, False),   # 15.6 / 10.7
+    ((400, 300), 3, 3, "f64", True, True, False),    # 15.1 / 11.5
+    ((768, 640), 3, 3, "f32", True, False, False),   # 13.9 / 11.3
+    ((768, 640), 2, 3, "f32", False, True, False),   # 7.6 / 6.4
+    ((512, 512), 3, 3, "f32", True, False, True),    # 9.2 / 9.9
+    ((64, 64), 3, 3, "f64", True, True, True),       # 4.4 / 6.9
+    ((512, 512), 2, 2, "f64", False, False, True),   # 4.1 / 4.5
+])
+def test_tiles_only_where_they_are_faster(state, n, N, K, precision, aniso, ext, tiles):
+    p, _, _ = inputs.random_instance(np.random.default_rng(7), 16, 16, N, K, nuclei=1)
+    p = p.copy(n=(n[0], n[1], 1), precision=precision)
+    if aniso:
+        p.delta[:, :] = 0.02 * (1.0 - np.eye(3))
+    if ext:
+        p.Bt[:N, :K - 1] = 0.05
+    p.dt = 0.2 * inputs.dt_limit(p)
+    assert (abi.mp_get_launches(state(p), 24)[3] > 0) == tiles
