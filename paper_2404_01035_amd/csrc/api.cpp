@@ -498,7 +498,10 @@ int vec_of(const mp_state* st, const Inst& I) {
 // A periodic row of 64 lanes' cells exactly is one strip without halo lanes
 // (strip_ring of the kernels).  Measured, 64 instances, 20 steps, against the
 // strips of 60 lanes: 64 x 1024 FP32 887 -> 543 us and FP64 1475 -> 906, 128 x
-// 1024 FP32 at two cells per lane 1489 -> 969, 64 x 64 FP32 133 -> 100.
+// 1024 FP32 at two cells per lane 1489 -> 969, 64 x 64 FP32 133 -> 100.  It serves
+// sweeps whose members all have that width; an ensemble of mixed widths hardly
+// holds one (64 members of 64 to 1024 cells a side: no difference), rows of other
+// widths up to 64 lanes would need the lane moves to rotate within the row.
 int strips_of(const mp_state* st, const Inst& I, bool rings = true) {
     const int v = vec_of(st, I);
     if (rings && I.grid.bc[0] == MP_BC_PERIODIC && I.grid.n[0] == 64 * v) return 1;
@@ -1098,7 +1101,9 @@ int make_step_call(mp_state* st, int kstep, int from, mp::KernelCall& k, int fus
 // next launch reads it, so its stores go past the caches and leave the L2s to
 // the halo rows that neighbouring tiles share: 512^3 FP32 (1.6 GB) 897 -> 873
 // us, 256^3 FP64 of five fields (671 MB) 315 -> 302; a state that the cache
-// holds loses by it, 200^3 FP32 of five fields (160 MB) 105 -> 112 us.
+// holds loses by it, 200^3 FP32 of five fields (160 MB) 105 -> 112 us.  Plain 3D
+// steps only: the general and the diagnostics instances were not measured with
+// it and store through the caches.
 constexpr double kCachedBytes = 256.0 * 1024 * 1024;
 
 // Single-grid launch of `fuse` steps from ``in`` to ``out`` at time level
